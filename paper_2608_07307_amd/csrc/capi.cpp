@@ -478,7 +478,8 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     // the fan launch's unit list: room for every pass slot (each patch lists at
     // most its slots)
     L.total_units = L.fans_inline ? 0 : L.total_fan_slots;
-    // the work counters are 32-bit and overshoot their range by at most one per wave
+    // the work counters are 32-bit and overshoot their range by less than it (a wave takes
+    // at most a fourth of what is left)
     if (L.total_chunks > ((int64_t)1 << 31))
         return fail(SRP_ERR_ARG, "batch too large: more than 2^31 chunks (split it or raise patches per chunk)");
     if (L.total_units > ((int64_t)1 << 31))

@@ -298,10 +298,10 @@ constexpr int WIN_STRIDE = 8;
 // counters QUEUE_STRIDE words apart; after both sets, the count of fan units
 // the trace kernel listed (FAN_UNITS_AT)
 // (launch_window zeroes them).
-constexpr int N_QUEUES = 8;
-constexpr int QUEUE_STRIDE = 64;
+constexpr int N_QUEUES = 64;      // (one lane per counter when a wave looks at all of them)
+constexpr int QUEUE_STRIDE = 8;   // (128-byte spacing measured the same)
 constexpr int FAN_UNITS_AT = 2 * N_QUEUES * QUEUE_STRIDE;
-constexpr int QUEUE_WORDS = FAN_UNITS_AT + QUEUE_STRIDE;
+constexpr int QUEUE_WORDS = FAN_UNITS_AT + 64;
 int launch_window(const EvalDesc *d_desc, int n_evals, int blocks_x, uint64_t *d_win, uint32_t *d_queue,
                   void *stream);
 // Builds n_jobs articulation slots, one thread each (articulate.hip); the
