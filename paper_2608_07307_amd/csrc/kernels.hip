@@ -49,6 +49,7 @@ constexpr int HWREG_XCC_ID = 20;   // hardware register holding the wave's XCD (
 #define SRP_WPE_GRAD 4
 #endif
 constexpr int MAX_CHAIN = SRP_MAX_BOUNCES + 1;
+constexpr size_t GRID_LDS = (BLOCK / 64) * 4 * sizeof(float4);   // the waves' ray grids (k_trace)
 
 // x from another lane of the same 16-lane row (data-parallel primitive move,
 // one per 32-bit half).  Every lane of the wave must be active.
@@ -63,7 +64,7 @@ __device__ __forceinline__ double readlane_f64(double x, int lane) {
                             __builtin_amdgcn_readlane(__double2loint(x), lane));
 }
 
-// Wave-wide sum, OR and maximum of 32-bit integers, returned to every lane
+// Wave-wide sum and maximum of 32-bit integers, returned to every lane
 // (quads, then rows by rotation, then the rows' first lanes).  Every lane of
 // the wave must be active.
 template <int CTRL>
@@ -79,13 +80,6 @@ __device__ __forceinline__ uint32_t wave_add_u32(uint32_t x) {
     x += dpp_u32<0x124>(x);
     x += dpp_u32<0x128>(x);
     return rows_u32(x, 0) + rows_u32(x, 16) + rows_u32(x, 32) + rows_u32(x, 48);
-}
-__device__ __forceinline__ uint32_t wave_or_u32(uint32_t x) {
-    x |= dpp_u32<0xB1>(x);
-    x |= dpp_u32<0x4E>(x);
-    x |= dpp_u32<0x124>(x);
-    x |= dpp_u32<0x128>(x);
-    return rows_u32(x, 0) | rows_u32(x, 16) | rows_u32(x, 32) | rows_u32(x, 48);
 }
 __device__ __forceinline__ int wave_max_i32(int x) {
     x = max(x, (int)dpp_u32<0xB1>((uint32_t)x));
@@ -110,10 +104,37 @@ __device__ __forceinline__ float wave_sum_f32(float x) {
     return (r0 + r1) + (r2 + r3);
 }
 
-// The sum of x over the wave's 64 lanes, returned to every lane, in a fixed
-// order: quads (lane ^ 1, then lane ^ 2), the four quads of each row (row
-// rotations by 4 and 8), then the four rows' totals as read from their first
-// lanes, ((r0 + r1) + (r2 + r3)).  Every lane of the wave must be active.
+// Orders this wave's earlier LDS accesses before its later ones across lanes
+// (one wave's LDS operations execute in issue order; this keeps the compiler
+// from reordering them).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The six sums over the wave's 64 lanes of the lanes' LDS accumulators (lane
+// 0's at acc, component k at acc[k * BLOCK + lane]), in a fixed order: quads
+// ((0 + 1) + (2 + 3)), the four quads of each 16 lanes ((0 + 3) + (2 + 1)), the
+// four of those ((0 + 1) + (2 + 3)).  Eight lanes share a component and add
+// eight accumulators each, so lane 8 k (and the seven after it) returns the
+// sum of component k: about 30 instructions, against 170 for six butterflies
+// over all 64 lanes (with the ray grid in LDS, below: 64 x 1024^2 forward 3.30 -> 3.11 ms,
+// with the adjoint 4.26 -> 3.98).  Lanes 48..63 return nothing of use.  Every lane of the
+// wave must be active; the accumulators' last writes come first.
+__device__ __forceinline__ double wave_sums6(const double *acc, int lane) {
+    wave_lds_fence();
+    const double2 *p = reinterpret_cast<const double2 *>(acc + min(lane >> 3, 5) * BLOCK + (lane & 7) * 8);
+    const double2 a = p[0], b = p[1], c = p[2], d = p[3];
+    const double q0 = (a.x + a.y) + (b.x + b.y), q1 = (c.x + c.y) + (d.x + d.y);
+    double x = q0 + dpp_f64<0xB1>(q1);   // even lanes: quads 0 + 3, odd ones: 2 + 1 (quad_perm (1, 0, 3, 2))
+    x += dpp_f64<0xB1>(x);
+    x += dpp_f64<0x4E>(x);               // (quad_perm (2, 3, 0, 1))
+    x += dpp_f64<0x141>(x);              // the other quad of the eight lanes (row_half_mirror)
+    return x;
+}
+
+// The sum of x over the wave's 64 lanes, returned to every lane, in the same
+// order as wave_sums6.  Every lane of the wave must be active.
 __device__ __forceinline__ double wave_sum(double x) {
     x += dpp_f64<0xB1>(x);    // quad_perm (1, 0, 3, 2)
     x += dpp_f64<0x4E>(x);    // quad_perm (2, 3, 0, 1)
@@ -165,14 +186,6 @@ __device__ __forceinline__ void lds_add(double *p, double v) {
 // A wave-uniform float held in a scalar register.
 __device__ __forceinline__ float uniform_f32(float x) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
-
-// Orders this wave's earlier LDS accesses before its later ones across lanes
-// (one wave's LDS operations execute in issue order; this keeps the compiler
-// from reordering them).
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 // Whether every triangle of node k lies in one plane (a ray leaving one of
@@ -329,6 +342,14 @@ __device__ __forceinline__ uint32_t take_work(WorkQueue &q, uint32_t *counters, 
     }
 }
 
+// Writes a wave's partial sums: the sum of component k from lane 8 k.
+__device__ __forceinline__ void store_partial(PatchOut *out, double tot, uint32_t hits, uint32_t sec, uint32_t sec_hits,
+                                              uint32_t flags, int lane) {
+    PatchOut SRP_GLOBAL *o = (PatchOut SRP_GLOBAL *)out;
+    if ((lane & 7) == 0 && lane < 48) o->f[lane >> 3] = tot;
+    if (lane == 48) *(uint4 SRP_GLOBAL *)&o->hits = make_uint4(hits, sec, sec_hits, flags);
+}
+
 // Position of the (j+1)-th set bit of m (j < popcount(m)).
 __device__ __forceinline__ int nth_set_bit(uint64_t m, int j) {
     int pos = 0;
@@ -374,7 +395,7 @@ __device__ __forceinline__ void fan_passes(const EvalDesc &D, const TraceCtx &TC
     for (int pass = pass0; pass < PM; pass += step) {
         const int64_t slot_out = D.fan_base + p * PM + pass;
         uint32_t rays = 0, hits = 0, nbox = 0, ntri = 0, status = 0;
-        double tot[6] = {0, 0, 0, 0, 0, 0};
+        double tot = 0.0;   // lane 8 k: component k
         if (pass * WAVE < tasks) {
             for (int k = 0; k < 6; ++k) lacc[k * BLOCK] = 0.0;
             const int t = pass * WAVE + lane;
@@ -426,23 +447,17 @@ __device__ __forceinline__ void fan_passes(const EvalDesc &D, const TraceCtx &TC
                     }
                 }
             }
-            for (int k = 0; k < 6; ++k) tot[k] = wave_sum(lacc[k * BLOCK]);
+            tot = wave_sums6(lacc - lane, lane);
             rays = wave_add_u32(rays);
             hits = wave_add_u32(hits);
-            status = wave_or_u32(status);
+            status = __ballot(status != 0) ? SRP_STATUS_STACK : 0u;
             if (COUNT) {
                 nbox = wave_add_u32(nbox);
                 ntri = wave_add_u32(ntri);
             }
         }
+        store_partial(fan_out + slot_out, tot, 0, rays, hits, status, lane);
         if (lane == 0) {
-            PatchOut co;
-            for (int k = 0; k < 6; ++k) co.f[k] = tot[k];
-            co.hits = 0;
-            co.sec = rays;
-            co.sec_hits = hits;
-            co.flags = status;
-            fan_out[slot_out] = co;
             if (COUNT) {
                 fan_counts[2 * slot_out] = nbox;
                 fan_counts[2 * slot_out + 1] = ntri;
@@ -475,7 +490,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
     uint32_t *lchain = reinterpret_cast<uint32_t *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK +
                                                     sizeof(double) * 6 * BLOCK) + tid;
     double *gw = reinterpret_cast<double *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK +
-                                            sizeof(uint32_t) * MAX_CHAIN * BLOCK) +
+                                            sizeof(uint32_t) * MAX_CHAIN * BLOCK + GRID_LDS) +
                  (size_t)wv * lds_grad_doubles;
 
     // Every wave is persistent on its own and takes chunks from the work queues
@@ -485,7 +500,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
     WorkQueue wq = work_queue(wv);
     int cur = -1;                          // evaluation of the previous chunk
     uint32_t cur_begin = 0, cur_end = 0;   // its chunk range
-    float o0[3], su[3], sv[3], dd[3];      // its ray grid (FP32 constants)
+    // its ray grid: origin o0, steps su and sv, direction dd (3 floats each, a float4
+    // apart) in LDS, read per patch (in registers they were spilled and reloaded)
+    float4 *grid = reinterpret_cast<float4 *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK +
+                                              (GRAD ? sizeof(uint32_t) * MAX_CHAIN * BLOCK : 0)) + 4 * wv;
     float tmin2 = 0.0f;
     bool empty = true;
     #pragma unroll 1
@@ -505,23 +523,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
             cur_end = (uint32_t)chunk_base[lo + 1];
             const EvalDesc &D = descs[lo];
             // window -> ray grid (FP64 -> FP32 constants)
-            const uint64_t *W = win + (size_t)lo * WIN_STRIDE;
-            const double umin = dec_f64(W[0]), umax = -dec_f64(W[1]);
-            const double vmin = dec_f64(W[2]), vmax = -dec_f64(W[3]), hmin = dec_f64(W[4]);
-            const double wu = umax - umin, wv_ = vmax - vmin;
-            empty = !(wu * wv_ > 0.0) || !(wu < INFINITY) || !(wv_ < INFINITY) || D.root_ref == REF_NONE;
-            const double L = fmax(wu, wv_);
-            const double h0 = hmin - 1e-3 * L - 1e-3;
-            const double du = wu / D.n, dv = wv_ / D.n;
-            // (wave-uniform values computed on the vector unit: moved to scalar registers)
-            for (int k = 0; k < 3; ++k) {
-                o0[k] = uniform_f32((float)((umin + 0.5 * du) * D.u[k] + (vmin + 0.5 * dv) * D.v[k] + h0 * D.d[k]));
-                su[k] = uniform_f32((float)(du * D.u[k]));
-                sv[k] = uniform_f32((float)(dv * D.v[k]));
-                dd[k] = uniform_f32((float)D.d[k]);
+            const RayGrid G = ray_grid(D, win + (size_t)lo * WIN_STRIDE);
+            if (lane == 0) {
+                grid[0] = make_float4(G.o0[0], G.o0[1], G.o0[2], 0.0f);
+                grid[1] = make_float4(G.su[0], G.su[1], G.su[2], 0.0f);
+                grid[2] = make_float4(G.sv[0], G.sv[1], G.sv[2], 0.0f);
+                grid[3] = make_float4(G.dd[0], G.dd[1], G.dd[2], 0.0f);
             }
-            tmin2 = uniform_f32((float)(1e-6 * L));
-            empty = __builtin_amdgcn_readfirstlane((int)empty) != 0;
+            wave_lds_fence();
+            tmin2 = uniform_f32(G.tmin2);
+            empty = __builtin_amdgcn_readfirstlane((int)G.empty) != 0;
         }
         const EvalDesc &D = descs[cur];
         const int64_t kc = c - cur_begin;
@@ -570,7 +581,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                 const bool valid = !empty && inside;
                 const int64_t pix = (int64_t)py * N + px;
                 int K = 0;
-                float d[3] = {dd[0], dd[1], dd[2]}, w = 1.0f;   // the current ray's direction and weight
+                const float4 g3 = grid[3];
+                float d[3] = {g3.x, g3.y, g3.z}, w = 1.0f;   // the current ray's direction and weight
                 bool cont = false;                              // the last chain hit spawned a specular ray
                 uint32_t emitted = 0;                           // generations whose hit emitted a fan
                 if (inside && D.hit_ids) {   // rays that are not traced or miss stay "no hit"
@@ -581,7 +593,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                 }
                 if (valid) {
                     float o[3];
-                    for (int k = 0; k < 3; ++k) o[k] = fmaf((float)py, sv[k], fmaf((float)px, su[k], o0[k]));
+                    const float4 g0 = grid[0], g1 = grid[1], g2 = grid[2];
+                    o[0] = fmaf((float)py, g2.x, fmaf((float)px, g1.x, g0.x));
+                    o[1] = fmaf((float)py, g2.y, fmaf((float)px, g1.y, g0.y));
+                    o[2] = fmaf((float)py, g2.z, fmaf((float)px, g1.z, g0.z));
                     float tmin = 0.0f;
                     int32_t excl = -1, skip = -1;   // the triangle and the planar instance the ray leaves
                     int gen = 0;   // chain generation
@@ -761,30 +776,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                 }
             }
 
-            // the patch's sums: wave reductions (every lane ends with the total), lane 0
-            // stores; a patch without a hit has zero sums (secondary hits need a primary)
-            double tot[6] = {0, 0, 0, 0, 0, 0};
-            if (__ballot((hcnt & 1023u) != 0))
-                for (int k = 0; k < 6; ++k) tot[k] = wave_sum(lacc[k * BLOCK]);
+            // the patch's sums; a patch without a hit has zero sums (secondary hits need a primary)
+            double tot = 0.0;   // lane 8 k: component k
+            if (__ballot((hcnt & 1023u) != 0)) tot = wave_sums6(lacc - lane, lane);
             hcnt = wave_add_u32(hcnt);
-            status = wave_or_u32(status);
+            status = __ballot(status != 0) ? SRP_STATUS_STACK : 0u;
+            const int64_t t = D.patch_base + pt;
+            store_partial(patches + t, tot, hcnt & 1023u, (hcnt >> 10) & 1023u, hcnt >> 20, status, lane);
             if (COUNT) {
                 nbox = wave_add_u32(nbox);
                 ntri = wave_add_u32(ntri);
-            }
-            const uint32_t cnts[6] = {hcnt & 1023u, (hcnt >> 10) & 1023u, hcnt >> 20, nbox, ntri, status};
-            if (lane == 0) {
-                PatchOut co;
-                for (int k = 0; k < 6; ++k) co.f[k] = tot[k];
-                co.hits = cnts[0];
-                co.sec = cnts[1];
-                co.sec_hits = cnts[2];
-                co.flags = cnts[5];
-                const int64_t t = D.patch_base + pt;
-                patches[t] = co;
-                if (COUNT) {
-                    counts[2 * t] = cnts[3];
-                    counts[2 * t + 1] = cnts[4];
+                if (lane == 0) {
+                    counts[2 * t] = nbox;
+                    counts[2 * t + 1] = ntri;
                 }
             }
             if (!GRAD && KD > 0 && fans_inline) {
@@ -1193,7 +1197,7 @@ int launch_window(const EvalDesc *d_desc, int n_evals, int blocks_x, uint64_t *d
 
 size_t trace_lds_bytes(bool grad, int lds_grad_doubles) {
     return sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK +
-           (grad ? sizeof(uint32_t) * MAX_CHAIN * BLOCK + sizeof(double) * (BLOCK / 64) * lds_grad_doubles : 0);
+           GRID_LDS + (grad ? sizeof(uint32_t) * MAX_CHAIN * BLOCK + sizeof(double) * (BLOCK / 64) * lds_grad_doubles : 0);
 }
 
 int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_evals, const uint64_t *d_win,

@@ -35,16 +35,23 @@ SRP_HD inline float safe_inv(float x) {
     return frame_rcp(ax);
 }
 
+// a . b with its roundings written out.
+SRP_HD inline float dot3(float a0, float a1, float a2, float b0, float b1, float b2) {
+#pragma clang fp contract(off)
+    return fmaf(a2, b2, fmaf(a0, b0, a1 * b1));
+}
+
 // An orthonormal basis (bx, by) orthogonal to unit d (Duff et al., JCGT 2017).
 SRP_HD inline void onb(const float d[3], float bx[3], float by[3]) {
+#pragma clang fp contract(off)
     float s = copysignf(1.0f, d[2]);
     float a = -frame_rcp(s + d[2]);
     float b = d[0] * d[1] * a;
-    bx[0] = 1.0f + s * d[0] * d[0] * a;
+    bx[0] = fmaf(s * d[0] * d[0], a, 1.0f);
     bx[1] = s * b;
     bx[2] = -s * d[0];
     by[0] = b;
-    by[1] = s + d[1] * d[1] * a;
+    by[1] = fmaf(d[1] * d[1], a, s);
     by[2] = -d[1];
 }
 
@@ -68,6 +75,13 @@ SRP_HD inline void near_planes(float ix, float iy, float iz, int &nx, int &ny, i
     nz = iz < 0.0f ? 5 : 2;
 }
 
+// The watertight test's offsets for a ray origin.
+SRP_HD inline void frame_offsets(const float o[3], Frame &F) {
+    F.cx = dot3(F.mx[0], F.mx[1], F.mx[2], o[0], o[1], o[2]);
+    F.cy = dot3(F.my[0], F.my[1], F.my[2], o[0], o[1], o[2]);
+    F.cz = dot3(F.mz[0], F.mz[1], F.mz[2], o[0], o[1], o[2]);
+}
+
 SRP_HD inline void frame_setup(const float o[3], const float d[3], Frame &F) {
     F.ix = safe_inv(d[0]);
     F.iy = safe_inv(d[1]);
@@ -78,9 +92,7 @@ SRP_HD inline void frame_setup(const float o[3], const float d[3], Frame &F) {
     near_planes(F.ix, F.iy, F.iz, F.nx, F.ny, F.nz);
     onb(d, F.mx, F.my);
     F.mz[0] = d[0]; F.mz[1] = d[1]; F.mz[2] = d[2];
-    F.cx = F.mx[0] * o[0] + F.mx[1] * o[1] + F.mx[2] * o[2];
-    F.cy = F.my[0] * o[0] + F.my[1] * o[1] + F.my[2] * o[2];
-    F.cz = F.mz[0] * o[0] + F.mz[1] * o[1] + F.mz[2] * o[2];
+    frame_offsets(o, F);
 }
 
 // Slab test of one box against [tmin, tmax] with its planes already ordered
@@ -150,6 +162,42 @@ constexpr uint32_t MAX_VISITS = 1u << 22;
 #else
 #define SRP_GLOBAL
 #endif
+
+// The primary rays of an evaluation: ray (px, py) starts at
+// fma(py, sv, fma(px, su, o0)) along dd.
+struct RayGrid {
+    float o0[3], su[3], sv[3], dd[3];
+    float tmin2;             // smallest hit distance of secondary rays
+    double umin, vmin, du, dv;
+    bool empty;              // nothing to trace
+};
+
+// From the evaluation's window W (enc_f64 bounds).  The roundings are written
+// out: every kernel that forms these rays forms the same bits.
+SRP_HD inline RayGrid ray_grid(const EvalDesc &D, const uint64_t *W) {
+#pragma clang fp contract(off)
+    RayGrid G;
+    const double umin = dec_f64(W[0]), umax = -dec_f64(W[1]);
+    const double vmin = dec_f64(W[2]), vmax = -dec_f64(W[3]), hmin = dec_f64(W[4]);
+    const double wu = umax - umin, wv = vmax - vmin;
+    G.empty = !(wu * wv > 0.0) || !(wu < INFINITY) || !(wv < INFINITY) || D.root_ref == REF_NONE;
+    const double L = fmax(wu, wv);
+    const double h0 = fma(-1e-3, L, hmin) - 1e-3;
+    const double du = wu / D.n, dv = wv / D.n;
+    const double a = fma(0.5, du, umin), b = fma(0.5, dv, vmin);
+    for (int k = 0; k < 3; ++k) {
+        G.o0[k] = (float)fma(h0, D.d[k], fma(a, D.u[k], b * D.v[k]));
+        G.su[k] = (float)(du * D.u[k]);
+        G.sv[k] = (float)(dv * D.v[k]);
+        G.dd[k] = (float)D.d[k];
+    }
+    G.tmin2 = (float)(1e-6 * L);
+    G.umin = umin;
+    G.vmin = vmin;
+    G.du = du;
+    G.dv = dv;
+    return G;
+}
 
 // What one traversal needs from an evaluation's descriptor, held in registers.
 struct TraceCtx {
@@ -288,12 +336,10 @@ SRP_HD inline bool trace_closest(const TraceCtx &C, const float o[3], const floa
                 const Inst SRP_GLOBAL &I = C.inst[inst];
                 float lo[3], ld[3];
                 const float r0 = o[0] - I.t[0], r1 = o[1] - I.t[1], r2 = o[2] - I.t[2];
-                lo[0] = I.R[0] * r0 + I.R[3] * r1 + I.R[6] * r2;
-                lo[1] = I.R[1] * r0 + I.R[4] * r1 + I.R[7] * r2;
-                lo[2] = I.R[2] * r0 + I.R[5] * r1 + I.R[8] * r2;
-                ld[0] = I.R[0] * d[0] + I.R[3] * d[1] + I.R[6] * d[2];
-                ld[1] = I.R[1] * d[0] + I.R[4] * d[1] + I.R[7] * d[2];
-                ld[2] = I.R[2] * d[0] + I.R[5] * d[1] + I.R[8] * d[2];
+                for (int k = 0; k < 3; ++k) {
+                    lo[k] = dot3(I.R[k], I.R[3 + k], I.R[6 + k], r0, r1, r2);
+                    ld[k] = dot3(I.R[k], I.R[3 + k], I.R[6 + k], d[0], d[1], d[2]);
+                }
                 frame_setup(lo, ld, F);
                 nodes = C.blas;
                 ref = I.root;
