@@ -26,6 +26,7 @@ struct srp_scene {
     float *d_mats = nullptr;
     WPoint *d_wpts = nullptr;
     int32_t *d_parent = nullptr;
+    int32_t *d_leaf_of = nullptr;  // leaf-order index of every original triangle index
     ArtNode *d_art = nullptr;      // the tree as the articulation kernel reads it
     BNode4 *d_topo = nullptr;      // top-level topology (references; boxes refitted per slot)
     char *d_slot = nullptr;        // current articulation slot
@@ -318,6 +319,15 @@ struct Layout {
     std::vector<int> grad_n;   // gradient partial doubles per chunk of each item (allocation and kernel)
     std::vector<int> item_ppc;   // patches per chunk of each item (the adjoint: its gradient group)
     int grid = 1, fan_grid = 0, wb = 1;
+    // primary hits by rasterisation (k_primary): the items it serves, their first
+    // patch in its buffers, its tile and the most tiles of any item
+    bool allow_vis = true;
+    std::vector<char> item_vis;
+    std::vector<int64_t> vis_base;
+    std::vector<size_t> prim_off;
+    int64_t vis_patches = 0;
+    int vis_tile = 0, vis_tiles = 0;
+    size_t o_vis = 0, o_vmask = 0;
     bool fans_inline = false;   // the trace kernel traces the fans itself (no fan launch)
     // captured forward plans of one patch per chunk: the patch order of the next
     // launch and the per-patch costs it is made from (layout_add_order)
@@ -403,7 +413,28 @@ Schedule pick_schedule(const srp_batch_item *items, int64_t n, bool grad, int64_
     return s;
 }
 
-int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule force, Layout *Lp) {
+// Primary hits by rasterisation (k_primary) instead of the trace kernel's
+// traversal; both find the same hits.  Measured whole launches at B = 1, traversal
+// against rasterisation, in us: 200k triangles at 800^2 (0.31 triangles per
+// pixel, 6 evaluations) 637 / 547, 300k of the 65-node craft (0.47) 370 / 395, 20k
+// at 300^2 (0.22, 46 evaluations) 493 / 414, 200k at 300^2 (2.2) 742 / 890, at 64^2
+// (49) 1058 / 3207: a tile tests every triangle it meets, a ray only a few.  A
+// launch of few patches (one evaluation) waits for its slowest tile, then for its
+// slowest patch: 20k at 300^2, 2 evaluations 172 / 162, but one evaluation of the
+// 50k craft at 512^2, whose captured launch starts its slowest patches first, 120 /
+// 139, at 900^2 even.  The 16 triangles of the box-wing gain nothing (205 / 210).
+bool use_raster(const srp_batch_item &it) {
+    return it.scene->h.n_tris >= 64 && 4 * it.scene->h.n_tris <= (int64_t)it.p.n * it.p.n;
+}
+constexpr int64_t RASTER_MIN_PATCHES = 16384;
+
+// The rasteriser's tile: smaller ones shorten the slowest tile of a small launch
+// (512^2 x 8 evaluations of 20k triangles: 1,287 us with 8 pixels, 1,304 with 16, 1,374
+// with 32), larger ones repeat less work (1024^2 x 64 of 50k: 3.07, 2.57 and 3.6 ms).
+int raster_tile(int64_t patches) { return patches >= 131072 ? 16 : 8; }
+
+int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule force, Layout *Lp,
+                 bool allow_vis = true) {
     Layout &L = *Lp;
     L = Layout();
     L.n = n;
@@ -574,6 +605,40 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         L.gslice_off[k] = goff;
         goff = align_up(goff + sizeof(double) * L.grad_n[k] * L.n_slices[k]);
     }
+    // primary hits
+    L.item_vis.assign(n, 0);
+    L.vis_base.assign(n, 0);
+    L.prim_off.assign(n, 0);
+    L.allow_vis = allow_vis;
+    if (allow_vis && !L.count) {   // (a counting launch counts the traversal's tests)
+        for (int64_t k = 0; k < n; ++k)
+            if (use_raster(items[k])) L.vis_patches += L.patch_base[k + 1] - L.patch_base[k];
+        if (L.vis_patches < RASTER_MIN_PATCHES) L.vis_patches = 0;
+        int64_t at = 0;
+        for (int64_t k = 0; k < n && L.vis_patches > 0; ++k) {
+            if (!use_raster(items[k])) continue;
+            L.item_vis[k] = 1;
+            L.vis_base[k] = at;
+            at += L.patch_base[k + 1] - L.patch_base[k];
+        }
+    }
+    if (L.vis_patches > 0) {
+        L.vis_tile = raster_tile(L.vis_patches);
+        const int pw = L.vis_tile / PATCH;
+        for (int64_t k = 0; k < n; ++k)
+            if (L.item_vis[k]) {
+                const int nt = (2 * L.tiles_x[k] + pw - 1) / pw;
+                L.vis_tiles = std::max(L.vis_tiles, nt * nt);
+            }
+        L.o_vmask = align_up(goff);
+        L.o_vis = align_up(L.o_vmask + sizeof(uint64_t) * L.vis_patches);
+        goff = align_up(L.o_vis + sizeof(uint2) * 64 * L.vis_patches);
+        for (int64_t k = 0; k < n; ++k) {
+            if (!L.item_vis[k]) continue;
+            L.prim_off[k] = goff;
+            goff = align_up(goff + sizeof(PrimaryEval) + sizeof(PrimaryInst) * items[k].scene->h.n_nodes);
+        }
+    }
     // persistent grids: one chunk (fan unit) per wave at a time, at most bpc resident
     // blocks per CU (the fan kernel: as many as fit)
     const int64_t waves = BLOCK / 64;
@@ -701,6 +766,14 @@ void staging_fill(const Layout &L, const srp_batch_item *items, const BatchOut &
         D.grad_part = L.grad ? reinterpret_cast<double *>(Dv + L.gpart_off[k]) : nullptr;
         D.n_slices = L.n_slices[k];
         D.slice_base = L.slice_base[k];
+        D.box_pad = (float)sc->h.pad;
+        if (L.item_vis[k]) {
+            D.vis = reinterpret_cast<uint2 *>(Dv + L.o_vis) + 64 * L.vis_base[k];
+            D.vis_mask = reinterpret_cast<uint64_t *>(Dv + L.o_vmask) + L.vis_base[k];
+            D.leaf_of = sc->d_leaf_of;
+            D.art = sc->d_art;
+            D.prim = reinterpret_cast<PrimaryEval *>(Dv + L.prim_off[k]);
+        }
         D.n_clamped = L.item_slot[k] >= 0 ? slot_clamped[L.item_slot[k]] : sc->cur.n_clamped;
         D.pslice = reinterpret_cast<SliceOut *>(Dv + L.pslice_off[k]);
         D.gslice = L.grad ? reinterpret_cast<double *>(Dv + L.gslice_off[k]) : nullptr;
@@ -741,6 +814,10 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
         int rc = prof_event_pair(&ev);
         if (rc) return rc;
         HIPCHK(hipEventRecord(ev.first, stream));
+    }
+    if (L.vis_patches > 0) {
+        e = launch_primary(d_desc, (int)L.n, d_win, L.vis_tile, L.vis_tiles, stream);
+        if (e) return fail(SRP_ERR_DEVICE, std::string("primary kernel: ") + hipGetErrorString((hipError_t)e));
     }
     PatchOut *d_fan_out = nullptr;
     uint64_t *d_fan_counts = nullptr;
@@ -800,7 +877,13 @@ int run_batch(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
         HIPCHK(hipEventSynchronize(g_ws.copied));
         HIPCHK(hipStreamWaitEvent(stream, g_ws.done, 0));
     }
-    if ((rc = ws_reserve(L.dev_bytes, L.stage_bytes))) return rc;   // (waits for the last batch to grow)
+    rc = ws_reserve(L.dev_bytes, L.stage_bytes);   // (waits for the last batch to grow)
+    if (rc == SRP_ERR_OOM && L.vis_patches > 0) {
+        // no room for the rasterised hits: trace the primary rays
+        if ((rc = layout_build(items, n, grad, force, &L, false))) return rc;
+        rc = ws_reserve(L.dev_bytes, L.stage_bytes);
+    }
+    if (rc) return rc;
     staging_fill(L, items, bo, g_ws.h_stage, g_ws.d_buf);
     if ((rc = enqueue(L, g_ws.d_buf, g_ws.h_stage, L.stage_bytes, bo, stream, g_prof.on, g_ws.copied))) return rc;
     HIPCHK(hipEventRecord(g_ws.done, stream));
@@ -870,10 +953,16 @@ int plan_make(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
     PlanImpl *P = new (std::nothrow) PlanImpl();
     if (!P) return fail(SRP_ERR_OOM, "host allocation failed");
     P->bo = bo;
-    if ((rc = layout_build(items, n, grad, Schedule(), &P->L))) { plan_free(P); return rc; }
-    layout_add_order(P->L);
-    if (hipMalloc(&P->d_buf, std::max<size_t>(P->L.dev_bytes, 256)) != hipSuccess) {
+    // (rasterised hits only while the plan's own buffer stays within the workspace cap and fits)
+    for (bool vis : {true, false}) {
+        if ((rc = layout_build(items, n, grad, Schedule(), &P->L, vis))) { plan_free(P); return rc; }
+        layout_add_order(P->L);
+        const bool retry = vis && P->L.vis_patches > 0;
+        if (retry && P->L.dev_bytes > WORKSPACE_CAP) continue;
+        if (hipMalloc(&P->d_buf, std::max<size_t>(P->L.dev_bytes, 256)) == hipSuccess) break;
         (void)hipGetLastError();
+        P->d_buf = nullptr;
+        if (retry) continue;
         plan_free(P);
         return fail(SRP_ERR_OOM, "plan device allocation failed");
     }
@@ -929,7 +1018,7 @@ int plan_refill(PlanImpl *P, const srp_batch_item *items, int64_t n, bool *compa
     int rc = check_items(items, n, P->L.grad, P->bo);
     if (rc) return rc;
     Layout L2;
-    if ((rc = layout_build(items, n, P->L.grad, P->L.sch, &L2))) return rc;
+    if ((rc = layout_build(items, n, P->L.grad, P->L.sch, &L2, P->L.allow_vis))) return rc;
     if (P->L.ordered) layout_add_order(L2);
     const Layout &L = P->L;
     if (L2.n != L.n || L2.stage_bytes != L.stage_bytes || L2.dev_bytes > L.dev_bytes || L2.grid != L.grid ||
@@ -942,6 +1031,7 @@ int plan_refill(PlanImpl *P, const srp_batch_item *items, int64_t n, bool *compa
         L2.o_emask != L.o_emask || L2.o_fanout != L.o_fanout || L2.o_fancnt != L.o_fancnt ||
         L2.o_queue != L.o_queue || L2.o_spill != L.o_spill || L2.slots.size() != L.slots.size() ||
         L2.o_jobs != L.o_jobs || L2.o_cs != L.o_cs || L2.o_slots != L.o_slots || L2.ordered != L.ordered ||
+        L2.item_vis != L.item_vis || L2.vis_tile != L.vis_tile || L2.o_vis != L.o_vis || L2.o_vmask != L.o_vmask ||
         L2.o_order != L.o_order || L2.o_cost != L.o_cost)
         return SRP_OK;
     for (size_t q = 0; q < L.slots.size(); ++q)
@@ -972,6 +1062,7 @@ void free_scene(srp_scene *sc) {
     (void)hipFree(sc->d_mats);
     (void)hipFree(sc->d_wpts);
     (void)hipFree(sc->d_parent);
+    (void)hipFree(sc->d_leaf_of);
     (void)hipFree(sc->d_art);
     (void)hipFree(sc->d_topo);
     (void)hipFree(sc->d_slot);
@@ -1108,7 +1199,9 @@ int srp_build_scene(const double *verts, int64_t n_verts, const int32_t *tris, i
     sc->device = g_ws.device;
     sc->angles.assign(sc->h.n_dof, 0.0);
     sc->slot_L = slot_layout(sc->h.n_nodes, std::max((int)sc->h.tlas_topo.size(), 1), sc->h.n_dof);
-    if ((rc = dev_upload(&sc->d_tris, sc->h.tris)) || (rc = dev_upload(&sc->d_blas, sc->h.blas)) ||
+    std::vector<int32_t> leaf_of((size_t)sc->h.n_tris, 0);
+    for (size_t i = 0; i < sc->h.tris.size(); ++i) leaf_of[(size_t)sc->h.tris[i].id] = (int32_t)i;
+    if ((rc = dev_upload(&sc->d_leaf_of, leaf_of)) || (rc = dev_upload(&sc->d_tris, sc->h.tris)) || (rc = dev_upload(&sc->d_blas, sc->h.blas)) ||
         (rc = dev_upload(&sc->d_mats, sc->h.mats)) || (rc = dev_upload(&sc->d_wpts, sc->h.wpts)) ||
         (rc = dev_upload(&sc->d_parent, sc->h.parent)) || (rc = dev_upload(&sc->d_art, art_nodes(sc->h))) ||
         (rc = dev_upload(&sc->d_topo, sc->h.tlas_topo))) {
@@ -1229,6 +1322,10 @@ int srp_eval_batch_noalloc(const srp_batch_item *items, int64_t n_items, srp_res
     if (rc) return rc;
     Layout L;
     if ((rc = layout_build(items, n_items, false, Schedule(), &L))) return rc;
+    // (rasterised hits only where they fit beside the whole grid's stacks)
+    if (L.vis_patches > 0 && L.dev_bytes > NOALLOC_SCRATCH_BYTES &&
+        (rc = layout_build(items, n_items, false, Schedule(), &L, false)))
+        return rc;
     if ((rc = layout_fit(&L, NOALLOC_SCRATCH_BYTES))) return rc;
     if (L.stage_bytes > NOALLOC_STAGE_BYTES)
         return fail(SRP_ERR_ARG, "batch too large for the fixed staging area: " + std::to_string(L.stage_bytes) +

@@ -561,14 +561,43 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
             wave_lds_fence();
         }
 
+        // Rasterised evaluations: the hit masks of the chunk's patches (lane i: patch
+        // p0 + i); patches without a hit get their zero sums here, one per lane,
+        // and are not visited (half of a spacecraft's image is empty)
+        const bool seen = D.vis != nullptr && !((const PrimaryEval SRP_CONST *)D.prim)->traced;
+        uint64_t hits = 0, visit = ~0ull;
+        if (seen) {
+            const int64_t mp = p0 + lane;
+            if (mp < p1) hits = ((const uint64_t SRP_GLOBAL *)D.vis_mask)[mp];
+            if (GRAD || KD == 0) {
+                visit = __ballot(hits != 0);
+                if (mp < p1 && hits == 0) {
+                    const PatchOut none = {};
+                    patches[D.patch_base + mp] = none;
+                    if (ORDERED && cost) ((uint32_t SRP_GLOBAL *)cost)[D.patch_base + mp] = 0u;
+                }
+            }
+        }
+
+        if (p1 - p0 < 64) visit &= (1ull << (int)(p1 - p0)) - 1ull;   // (p0 < p1 <= p0 + MAX_PPC)
+        uint2 next = make_uint2(0, 0);   // the next visited patch's first hits, read one patch
+                                         // ahead (the adjoint has no registers for it)
+        if (!GRAD && seen && visit)
+            next = ((const uint2 SRP_GLOBAL *)D.vis)[(p0 + __ffsll((unsigned long long)visit) - 1) * WAVE + lane];
         #pragma unroll 1
-        for (int64_t pt = p0; pt < p1; ++pt) {
+        while (visit) {
             // one 8x8 patch per iteration, one ray per lane; its sums go to the
             // patch's own slot, so the forward result does not depend on the
             // chunking or on which wave runs it
+            const int64_t pt = p0 + __ffsll((unsigned long long)visit) - 1;
+            visit &= visit - 1;
+            uint2 first = next;
+            if (!GRAD && seen && visit)
+                next = ((const uint2 SRP_GLOBAL *)D.vis)[(p0 + __ffsll((unsigned long long)visit) - 1) * WAVE + lane];
             const int tile = (int)(pt >> 2), q = (int)(pt & 3);
             const int px = (tile % D.tiles_x) * TILE + (q & 1) * PATCH + (lane & 7);
             const int py = (tile / D.tiles_x) * TILE + (q >> 1) * PATCH + (lane >> 3);
+            if (GRAD && seen) first = ((const uint2 SRP_GLOBAL *)D.vis)[pt * WAVE + lane];
             const uint64_t clock0 = (ORDERED && cost) ? wall_clock64() : 0;
             for (int k = 0; k < 6; ++k) lacc[k * BLOCK] = 0.0;
             // hit counts packed in 10-bit fields (primary hits, specular secondary rays and
@@ -578,7 +607,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
             uint64_t em[SRP_MAX_BOUNCES] = {};   // the patch's fan emitters per generation
             {
                 const bool inside = px < N && py < N;
-                const bool valid = !empty && inside;
+                const uint64_t hm =
+                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)hits, (int)(pt - p0)) |
+                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(hits >> 32), (int)(pt - p0)) << 32;
+                const bool valid = seen ? ((hm >> lane) & 1ull) != 0 : !empty && inside;
                 const int64_t pix = (int64_t)py * N + px;
                 int K = 0;
                 const float4 g3 = grid[3];
@@ -603,7 +635,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                     #pragma unroll 1
                     for (;;) {
                         Hit h;
-                        if (!trace_closest<COUNT>(TC, o, d, tmin, excl, skip, stack, h, nbox, ntri)) {
+                        if (seen && gen == 0) {
+                            h.t = __uint_as_float(first.x);
+                            h.tri = (int32_t)first.y;
+                            const TriRec SRP_GLOBAL &T = TC.tris[h.tri];
+                            h.inst = T.node;
+                            h.id = T.id;
+                        } else if (!trace_closest<COUNT>(TC, o, d, tmin, excl, skip, stack, h, nbox, ntri)) {
                             status |= SRP_STATUS_STACK;
                             break;
                         }

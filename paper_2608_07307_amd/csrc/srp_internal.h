@@ -49,6 +49,8 @@ constexpr int MAX_PPC = 64;                 // patches per chunk (one wave's wor
 constexpr int MAX_GRAD_SLOTS = 960;         // doubles per wave for gradient partials (LDS <= 64 KB)
 
 #define SRP_HD __host__ __device__
+// Memory that nothing writes during the kernel: its uniform reads are scalar loads.
+#define SRP_CONST __attribute__((address_space(4)))
 
 SRP_HD inline uint32_t make_ref(uint32_t type, uint32_t idx) { return (type << 30) | idx; }
 SRP_HD inline uint32_t ref_type(uint32_t r) { return r >> 30; }
@@ -164,6 +166,28 @@ struct alignas(16) ArtJob {
 };
 static_assert(sizeof(ArtJob) == 96, "ArtJob layout");
 
+// An evaluation's primary rays and, per instance, the map of its rest-pose
+// points to image coordinates (column X = u . p + uc, row Y = v . p + vc; pixel k's
+// ray at k), its frame of the photon direction and its image rectangle:
+// written by k_primary_setup, read by k_primary.
+struct alignas(64) PrimaryEval {
+    float o0[3], su[3], sv[3];   // ray (px, py) starts at fma(py, sv, fma(px, su, o0))
+    float mx, my;                // pixel margin: twice the hierarchy's box padding
+    int32_t empty;               // nothing to trace
+    int32_t traced;              // a sliver of a window: the trace kernel traces the primary rays
+    int32_t pad_[3];
+};
+static_assert(sizeof(PrimaryEval) == 64, "PrimaryEval layout");
+struct alignas(64) PrimaryInst {
+    float rect[4];               // x0, x1, y0, y1 of the node's padded box, widened by the margin
+    float u[3], uc, v[3], vc;
+    float R[9], t[3];            // the instance's transform
+    float mx[3], my[3], mz[3];   // its frame (trace.h)
+    uint32_t root;               // bottom-level root
+    uint32_t pad_[14];
+};
+static_assert(sizeof(PrimaryInst) == 192, "PrimaryInst layout");
+
 // One evaluation, as the kernels see it.
 struct alignas(64) EvalDesc {
     // scene
@@ -211,8 +235,14 @@ struct alignas(64) EvalDesc {
     SliceOut *pslice;       // n_slices range sums of the patch (and fan) partials
     int64_t slice_base;     // the batch's number of this evaluation's first range sum
     int32_t n_clamped;      // hinge angles of this evaluation clamped to their intervals
-    int32_t pad_;
+    float box_pad;          // padding of the hierarchies' boxes (metres)
     uint64_t planar[2];     // bit k: every triangle of node k lies in one plane (rays leaving it skip it)
+    // primary hits by k_primary (null: the trace kernel traces the primary rays)
+    uint2 *vis;             // n_patches x 64: distance bits, leaf-order triangle (where the mask is set)
+    uint64_t *vis_mask;     // n_patches: the patch's hit pixels
+    const int32_t *leaf_of; // T: leaf-order index of an original triangle index
+    const ArtNode *art;     // K tree nodes
+    PrimaryEval *prim;      // the image of this evaluation's instances: a PrimaryEval, then K PrimaryInst
 };
 
 // The host writes these records and the kernels read them: both compilation
@@ -264,6 +294,8 @@ static_assert(offsetof(EvalDesc, pslice) == 352, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, slice_base) == 360, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, n_clamped) == 368, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, planar) == 376, "EvalDesc layout");
+static_assert(offsetof(EvalDesc, vis) == 392, "EvalDesc layout");
+static_assert(offsetof(EvalDesc, leaf_of) == 408, "EvalDesc layout");
 static_assert(sizeof(PatchOut) == 64, "PatchOut layout");
 static_assert(offsetof(PatchOut, f) == 0, "PatchOut layout");
 static_assert(offsetof(PatchOut, hits) == 48, "PatchOut layout");
@@ -307,6 +339,10 @@ int launch_window(const EvalDesc *d_desc, int n_evals, int blocks_x, uint64_t *d
 // Builds n_jobs articulation slots, one thread each (articulate.hip); the
 // window kernel reads them, so it runs first on the same stream.
 int launch_articulate(const ArtJob *d_jobs, int n_jobs, void *stream);
+// Primary hits of the evaluations whose descriptor has vis, on tiles of tile x
+// tile pixels (16 or 8); max_tiles: the most tiles of any of them.  Runs
+// after the window kernel and before the trace kernel (primary.hip).
+int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, int tile, int max_tiles, void *stream);
 // d_spill: grid_blocks * BLOCK * STACK_SPILL words; chunk counts below 2^31.
 // d_fan_out, d_fan_counts (forward, diffuse rays on): the fan pass partial
 // slots.  With fans_inline the trace kernel also traces every patch's diffuse
