@@ -423,15 +423,17 @@ Schedule pick_schedule(const srp_batch_item *items, int64_t n, bool grad, int64_
 // slowest patch: 20k at 300^2, 2 evaluations 172 / 162, but one evaluation of the
 // 50k craft at 512^2, whose captured launch starts its slowest patches first, 120 /
 // 139, at 900^2 even.  The 16 triangles of the box-wing gain nothing (205 / 210).
-bool use_raster(const srp_batch_item &it) {
-    return it.scene->h.n_tris >= 64 && 4 * it.scene->h.n_tris <= (int64_t)it.p.n * it.p.n;
+// Launches that fill the chip with 16-pixel tiles gain up to more triangles per
+// pixel: 648 directions of the 50k craft at 300^2 (0.55) 3,186 / 2,643.
+bool use_raster(const srp_batch_item &it, double tris_per_pixel) {
+    return it.scene->h.n_tris >= 64 && (double)it.scene->h.n_tris <= tris_per_pixel * it.p.n * it.p.n;
 }
-constexpr int64_t RASTER_MIN_PATCHES = 16384;
+constexpr int64_t RASTER_MIN_PATCHES = 16384, RASTER_BIG_PATCHES = 131072;
 
 // The rasteriser's tile: smaller ones shorten the slowest tile of a small launch
 // (512^2 x 8 evaluations of 20k triangles: 1,287 us with 8 pixels, 1,304 with 16, 1,374
 // with 32), larger ones repeat less work (1024^2 x 64 of 50k: 3.07, 2.57 and 3.6 ms).
-int raster_tile(int64_t patches) { return patches >= 131072 ? 16 : 8; }
+int raster_tile(int64_t patches) { return patches >= RASTER_BIG_PATCHES ? 16 : 8; }
 
 int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule force, Layout *Lp,
                  bool allow_vis = true) {
@@ -611,12 +613,18 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     L.prim_off.assign(n, 0);
     L.allow_vis = allow_vis;
     if (allow_vis && !L.count) {   // (a counting launch counts the traversal's tests)
-        for (int64_t k = 0; k < n; ++k)
-            if (use_raster(items[k])) L.vis_patches += L.patch_base[k + 1] - L.patch_base[k];
-        if (L.vis_patches < RASTER_MIN_PATCHES) L.vis_patches = 0;
+        double ratio = 0.6;
+        for (int64_t least : {RASTER_BIG_PATCHES, RASTER_MIN_PATCHES}) {
+            L.vis_patches = 0;
+            for (int64_t k = 0; k < n; ++k)
+                if (use_raster(items[k], ratio)) L.vis_patches += L.patch_base[k + 1] - L.patch_base[k];
+            if (L.vis_patches >= least) break;
+            L.vis_patches = 0;
+            if (least == RASTER_BIG_PATCHES) ratio = 0.25;
+        }
         int64_t at = 0;
         for (int64_t k = 0; k < n && L.vis_patches > 0; ++k) {
-            if (!use_raster(items[k])) continue;
+            if (!use_raster(items[k], ratio)) continue;
             L.item_vis[k] = 1;
             L.vis_base[k] = at;
             at += L.patch_base[k + 1] - L.patch_base[k];
