@@ -317,7 +317,10 @@ struct Layout {
     std::vector<int64_t> slice_base;   // first range sum of every item, then the total
     std::vector<size_t> emit_off;   // emitter records of each item with diffuse fans (0: none)
     std::vector<int> grad_n;   // gradient partial doubles per chunk of each item (allocation and kernel)
-    std::vector<int> item_ppc;   // patches per chunk of each item (the adjoint: its gradient group)
+    int64_t max_groups = 0;
+    std::vector<int> group;      // adjoint: patches per gradient group of each item
+    std::vector<int64_t> n_groups;
+    std::vector<size_t> chain_off;
     int grid = 1, fan_grid = 0, wb = 1;
     // primary hits by rasterisation (k_primary): the items it serves, their first
     // patch in its buffers, its tile and the most tiles of any item
@@ -367,9 +370,8 @@ int check_items(const srp_batch_item *items, int64_t n, bool grad, const BatchOu
     return SRP_OK;
 }
 
-// The adjoint's gradient partials are per chunk, and an adjoint chunk is a
-// fixed group of an evaluation's patches whose size depends on that
-// evaluation alone (grad_group), never on the schedule: gradient bits then do
+// The adjoint's gradient partials are per group, a fixed run of an
+// evaluation's patches whose size depends on that evaluation alone (grad_group), never on the schedule: gradient bits then do
 // not depend on the autotuner, the blocks per CU or the batch around an
 // evaluation.  The group is the smallest power of two from GRAD_GROUP_MIN up
 // to MAX_PPC patches whose partials for the evaluation fit GRAD_PART_EVAL
@@ -385,8 +387,7 @@ int grad_group(int64_t n_patches, int grad_n) {
     return g;
 }
 
-Schedule pick_schedule(const srp_batch_item *items, int64_t n, bool grad, int64_t total_patches, int occ,
-                       int max_grad_n) {
+Schedule pick_schedule(const srp_batch_item *items, int64_t n, bool grad, int64_t total_patches, int occ) {
     Schedule s = g_override;
     if (!s.ppc || !s.bpc) {
         auto f = g_tuned.find(tune_key(items, n, grad));
@@ -468,18 +469,20 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         L.slice_base[k + 1] = L.slice_base[k] + L.n_slices[k];
     }
     if (L.slice_base[n] > INT32_MAX) return fail(SRP_ERR_ARG, "batch too large: more than 2^31 range sums (split it)");
-    int occ = trace_blocks_per_cu(L.count, grad, L.dir, L.max_grad_n);
-    L.sch = (force.ppc && force.bpc) ? force : pick_schedule(items, n, grad, L.total_patches, occ, L.max_grad_n);
+    int occ = trace_blocks_per_cu(L.count);
+    L.sch = (force.ppc && force.bpc) ? force : pick_schedule(items, n, grad, L.total_patches, occ);
     if (force.ppc) L.sch.ppc = force.ppc;
     if (force.bpc) L.sch.bpc = std::min(force.bpc, occ);
-    // patches per chunk: the schedule's for the forward launch, each evaluation's
-    // own gradient group for the adjoint
-    L.item_ppc.assign(n, L.sch.ppc);
+    L.group.assign(n, 0);
+    L.n_groups.assign(n, 0);
     for (int64_t k = 0; k < n; ++k) {
         const int64_t np = L.patch_base[k + 1] - L.patch_base[k];
-        if (grad) L.item_ppc[k] = grad_group(np, grad_slots(items[k].scene, items[k].p.flags));
         L.chunk_base[k] = L.total_chunks;
-        L.total_chunks += (np + L.item_ppc[k] - 1) / L.item_ppc[k];
+        L.total_chunks += (np + L.sch.ppc - 1) / L.sch.ppc;
+        if (!grad) continue;
+        L.group[k] = grad_group(np, grad_slots(items[k].scene, items[k].p.flags));
+        L.n_groups[k] = (np + L.group[k] - 1) / L.group[k];
+        L.max_groups = std::max(L.max_groups, L.n_groups[k]);
     }
     L.chunk_base[n] = L.total_chunks;
     // diffuse fans (forward only; emitters are chain hits of generation < bounces).
@@ -592,6 +595,7 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     }
     L.o_gpart = eoff;
     L.gpart_off.assign(n, 0);
+    L.chain_off.assign(n, 0);
     L.grad_n.assign(n, 0);
     L.gslice_off.assign(n, 0);
     L.pslice_off.assign(n, 0);
@@ -600,10 +604,12 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         L.pslice_off[k] = goff;
         goff = align_up(goff + sizeof(SliceOut) * L.n_slices[k]);
         if (!grad) continue;
-        const int64_t nc = L.chunk_base[k + 1] - L.chunk_base[k];
+        L.chain_off[k] = goff;
+        goff = align_up(goff + sizeof(uint32_t) * 64 * (size_t)(items[k].p.bounces + 1) *
+                                   (L.patch_base[k + 1] - L.patch_base[k]));
         L.gpart_off[k] = goff;
         L.grad_n[k] = grad_slots(items[k].scene, items[k].p.flags);
-        goff = align_up(goff + sizeof(double) * L.grad_n[k] * nc);
+        goff = align_up(goff + sizeof(double) * L.grad_n[k] * L.n_groups[k]);
         L.gslice_off[k] = goff;
         goff = align_up(goff + sizeof(double) * L.grad_n[k] * L.n_slices[k]);
     }
@@ -674,8 +680,7 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
 void layout_add_order(Layout &L) {
     // (launches of at most 2 blocks per CU: the kernel build that orders its work)
     if (L.grad || L.count || L.sch.bpc > 2 || L.total_patches <= 0) return;
-    for (int64_t k = 0; k < L.n; ++k)
-        if (L.item_ppc[k] != 1) return;
+    if (L.sch.ppc != 1) return;
     L.ordered = true;
     L.o_order = align_up(L.dev_bytes);
     L.o_cost = align_up(L.o_order + sizeof(uint32_t) * (size_t)(L.total_patches + 1));   // (+ launch count)
@@ -761,9 +766,10 @@ void staging_fill(const Layout &L, const srp_batch_item *items, const BatchOut &
         D.dset = it.p.n_diffuse > 0 ? g_ws.d_dset + 4 * dset_entry(it.p.n_diffuse) : nullptr;
         D.tiles_x = L.tiles_x[k];
         D.tiles_y = L.tiles_y[k];
-        D.ppc = L.item_ppc[k];
-        D.chunk_base = L.chunk_base[k];
-        D.n_chunks = L.chunk_base[k + 1] - L.chunk_base[k];
+        D.ppc = L.sch.ppc;
+        D.n_groups = L.n_groups[k];
+        D.group = L.group[k];
+        D.chain = L.grad ? reinterpret_cast<uint32_t *>(Dv + L.chain_off[k]) : nullptr;
         D.patch_base = L.patch_base[k];
         D.n_patches = L.patch_base[k + 1] - L.patch_base[k];
         const bool fans = L.fan_base[k + 1] > L.fan_base[k];
@@ -835,15 +841,18 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
     }
     int4 *d_units = L.total_units > 0 ? reinterpret_cast<int4 *>(Dv + L.o_units) : nullptr;
     e = launch_trace(d_desc, d_cbase, (int)L.n, d_win, L.total_chunks, d_queue, d_spill, d_patches, d_counts, L.count,
-                     L.grad, L.dir, L.grid, L.max_grad_n, d_fan_out, d_fan_counts, L.fans_inline, d_units, L.sch.bpc,
-                     d_order, d_cost, stream);
+                     L.grid, d_fan_out, d_fan_counts, L.fans_inline, d_units, L.sch.bpc, d_order, d_cost, stream);
     if (e) return fail(SRP_ERR_DEVICE, std::string("trace kernel: ") + hipGetErrorString((hipError_t)e));
     if (L.total_units > 0) {
         e = launch_fans(d_desc, d_win, L.total_units, d_queue, d_spill, d_fan_out, d_fan_counts, d_units, L.count,
                         L.fan_grid, stream);
         if (e) return fail(SRP_ERR_DEVICE, std::string("fan kernel: ") + hipGetErrorString((hipError_t)e));
     }
-    if (profile) {   // the ray-tracing kernels: trace, then fans
+    if (L.grad) {
+        e = launch_adjoint(d_desc, (int)L.n, L.max_groups, d_patches, L.dir, L.max_grad_n, stream);
+        if (e) return fail(SRP_ERR_DEVICE, std::string("adjoint kernel: ") + hipGetErrorString((hipError_t)e));
+    }
+    if (profile) {   // the ray kernels: primary hits, trace, then fans or the adjoint
         HIPCHK(hipEventRecord(ev.second, stream));
         g_prof.pairs.push_back(ev);
     }
@@ -1031,7 +1040,7 @@ int plan_refill(PlanImpl *P, const srp_batch_item *items, int64_t n, bool *compa
     const Layout &L = P->L;
     if (L2.n != L.n || L2.stage_bytes != L.stage_bytes || L2.dev_bytes > L.dev_bytes || L2.grid != L.grid ||
         L2.wb != L.wb || L2.count != L.count || L2.dir != L.dir || L2.max_grad_n != L.max_grad_n ||
-        L2.grad_n != L.grad_n || L2.chunk_base != L.chunk_base ||
+        L2.grad_n != L.grad_n || L2.chain_off != L.chain_off || L2.chunk_base != L.chunk_base ||
         L2.patch_base != L.patch_base || L2.o_patches != L.o_patches || L2.o_counts != L.o_counts ||
         L2.total_units != L.total_units || L2.fan_base != L.fan_base || L2.fan_grid != L.fan_grid ||
         L2.o_units != L.o_units || L2.fans_inline != L.fans_inline ||
@@ -1502,14 +1511,9 @@ int srp_autotune(const srp_batch_item *items, int64_t n_items, int32_t flags, in
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
-    bool cnt = false, dir = false;
-    int mg = 0;
-    for (int64_t k = 0; k < n_items; ++k) {
-        cnt |= (items[k].p.flags & SRP_F_COUNT) != 0;
-        dir |= grad && (items[k].p.flags & SRP_F_GRAD_DIR);
-        if (grad && items[k].scene) mg = std::max(mg, grad_slots(items[k].scene, items[k].p.flags));
-    }
-    int occ = trace_blocks_per_cu(cnt, grad, dir, mg);
+    bool cnt = false;
+    for (int64_t k = 0; k < n_items; ++k) cnt |= (items[k].p.flags & SRP_F_COUNT) != 0;
+    int occ = trace_blocks_per_cu(cnt);
     Schedule best;
     double best_t = INFINITY;
     int64_t total_patches = 0;
@@ -1518,24 +1522,21 @@ int srp_autotune(const srp_batch_item *items, int64_t n_items, int32_t flags, in
         total_patches += 4 * t * t;
     }
     // candidates: patches per chunk 1..64 (powers of two) that give every
-    // resident wave at least one chunk and at most 64, at full and half
-    // occupancy; the adjoint's chunks are its evaluations' gradient groups, so
-    // only the occupancy is tuned for it
+    // resident wave at least one chunk and at most 64, at full and half occupancy
     std::vector<Schedule> cands;
     for (int b : {occ, std::max(1, occ / 2)}) {
         const int64_t resident = (int64_t)g_ws.n_cu * b * (BLOCK / 64);
         for (int ppc = 1; ppc <= MAX_PPC; ppc *= 2) {
             const int64_t chunks = (total_patches + ppc - 1) / ppc;
-            if (!grad && ((chunks < resident && ppc > 1) || chunks > 64 * resident)) continue;
+            if ((chunks < resident && ppc > 1) || chunks > 64 * resident) continue;
             Schedule sc;
-            sc.ppc = grad ? GRAD_GROUP_MIN : ppc;
+            sc.ppc = ppc;
             sc.bpc = b;
             cands.push_back(sc);
-            if (grad) break;
         }
         if (b == 1) break;
     }
-    if (cands.empty()) cands.push_back(pick_schedule(items, n_items, grad, total_patches, occ, mg));
+    if (cands.empty()) cands.push_back(pick_schedule(items, n_items, grad, total_patches, occ));
     for (const Schedule &sc : cands) {
         double tmin = INFINITY;
         for (int rep = 0; rep < 5 && rc == 0; ++rep) {   // one warm-up, the best of four

@@ -14,9 +14,10 @@
 //             reduction, one partial per patch (no floating-point atomics, so
 //             results do not depend on scheduling).  With diffuse rays a chain
 //             hit that emits a fan writes an emitter record; for big batches
-//             the kernel then traces the patch's fan passes itself.  The GRAD
-//             variant also differentiates each ray's hit chain at fixed
-//             visibility.
+//             the kernel then traces the patch's fan passes itself.  For the
+//             adjoint it also records each pixel's hit chain.
+//   k_adjoint per group of patches, differentiates the recorded chains at
+//             fixed visibility.
 //   k_fans    small diffuse batches: the patches' fan passes as a separate
 //             persistent launch, each patch split into several work units.
 //   k_slices  one block per range sum (up to 16 per evaluation, numbered
@@ -28,6 +29,8 @@
 // The per-pixel structure, the iterative secondary rays and the GPU-side
 // reduction follow Sec. 4.3 of the paper; the articulation follows Sec. 4.4.
 #include <float.h>
+
+#include <algorithm>
 
 #include "srp.h"
 #include "srp_internal.h"
@@ -45,10 +48,6 @@ constexpr int HWREG_XCC_ID = 20;   // hardware register holding the wave's XCD (
 #ifndef SRP_WPE_FWD
 #define SRP_WPE_FWD 4
 #endif
-#ifndef SRP_WPE_GRAD
-#define SRP_WPE_GRAD 4
-#endif
-constexpr int MAX_CHAIN = SRP_MAX_BOUNCES + 1;
 constexpr size_t GRID_LDS = (BLOCK / 64) * 4 * sizeof(float4);   // the waves' ray grids (k_trace)
 
 // x from another lane of the same 16-lane row (data-parallel primitive move,
@@ -129,11 +128,13 @@ __device__ __forceinline__ double wave_sum(double x) {
     return (readlane_f64(x, 0) + readlane_f64(x, 16)) + (readlane_f64(x, 32) + readlane_f64(x, 48));
 }
 
-// The adjoint keeps one word per hit of a lane's chain in LDS: the triangle's
-// leaf-order index, with the top bit set when the geometric normal was flipped
-// to face the incoming ray.  The reverse sweep recomputes the normal from it
+// The adjoint's record of a pixel's chain is one word per hit: the triangle's
+// leaf-order index (below 2^27), with the top bit set when the geometric normal
+// was flipped to face the incoming ray; CHAIN_END after the last hit when it
+// is not the longest possible chain.  The sweep recomputes the normals from it
 // bit for bit and recovers each incoming direction and weight backwards from
 // the last ones (a mirror reflection is its own inverse).
+constexpr uint32_t CHAIN_END = 0xFFFFFFFFu;
 constexpr uint32_t CHAIN_FLIP = 0x80000000u;
 
 // *p += v as one LDS add, for accumulators that only this wave adds to (its
@@ -247,6 +248,36 @@ __device__ __forceinline__ bool hit_normal(const TraceCtx &TC, const EvalDesc &D
     rd = mats[2 * T.mat + 1];
     id = T.id;
     return flip;
+}
+
+// A recorded chain hit: its normal bit for bit as hit_normal formed it, its
+// material and node.  The triangle's record in one round trip, then its
+// instance's rotation and its material together.
+struct ChainHit {
+    float n[3], rs, rd;
+    int node, mat;
+};
+__device__ __forceinline__ ChainHit chain_hit(const TraceCtx &TC, const EvalDesc &D, uint32_t ew) {
+    ChainHit C;
+    const float4 SRP_GLOBAL *tq = (const float4 SRP_GLOBAL *)(TC.tris + (ew & ~CHAIN_FLIP));
+    const float4 T0 = tq[0], T1 = tq[1], T2 = tq[2];
+    C.node = f2i(T2.w);
+    C.mat = f2i(T1.w);
+    const Inst SRP_GLOBAL &I = TC.inst[C.node];
+    const float4 Ra = *(const float4 SRP_GLOBAL *)&I.R[0], Rb = *(const float4 SRP_GLOBAL *)&I.R[4];
+    const float R8 = I.R[8];
+    const float2 rm = ((const float2 SRP_GLOBAL *)D.mats)[C.mat];
+    const float IR[9] = {Ra.x, Ra.y, Ra.z, Ra.w, Rb.x, Rb.y, Rb.z, Rb.w, R8};
+    const float e1[3] = {T1.x - T0.x, T1.y - T0.y, T1.z - T0.z};
+    const float e2[3] = {T2.x - T0.x, T2.y - T0.y, T2.z - T0.z};
+    const float nl[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
+    for (int i = 0; i < 3; ++i) C.n[i] = IR[3 * i] * nl[0] + IR[3 * i + 1] * nl[1] + IR[3 * i + 2] * nl[2];
+    float inv = rsqrtf(C.n[0] * C.n[0] + C.n[1] * C.n[1] + C.n[2] * C.n[2]);
+    if (ew & CHAIN_FLIP) inv = -inv;
+    for (int i = 0; i < 3; ++i) C.n[i] *= inv;
+    C.rs = rm.x;
+    C.rd = rm.y;
+    return C;
 }
 
 // Adds force f at point x (and its torque about ref) to the lane's FP64 sums.
@@ -489,11 +520,11 @@ __device__ __forceinline__ void fan_passes(const EvalDesc &D, const TraceCtx &TC
 // WPE = 0: registers for the occupancy targets above (batches); WPE = 2: for
 // launches of at most 2 blocks per CU (single evaluations), which lose no
 // occupancy by it and keep every value in registers.
-template <bool COUNT, bool GRAD, bool DIR, int WPE = 0>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE : GRAD ? SRP_WPE_GRAD : SRP_WPE_FWD))) void k_trace(
+template <bool COUNT, int WPE = 0>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE : SRP_WPE_FWD))) void k_trace(
     const EvalDesc *__restrict__ descs, const int64_t *__restrict__ chunk_base, int n_evals,
     const uint64_t *__restrict__ win, int grid_blocks, int64_t total_chunks, uint32_t *queue, uint32_t *spill,
-    PatchOut *__restrict__ patches, uint64_t *__restrict__ counts, int lds_grad_doubles, int fans_inline,
+    PatchOut *__restrict__ patches, uint64_t *__restrict__ counts, int fans_inline,
     PatchOut *__restrict__ fan_out, uint64_t *__restrict__ fan_counts, int4 *__restrict__ fan_units,
     const uint32_t *__restrict__ order, uint32_t *__restrict__ cost) {
     extern __shared__ char smem[];
@@ -506,13 +537,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
     // per-lane FP64 force/torque sums of the current patch (component k at [k * BLOCK]):
     // kept in LDS and updated with LDS adds, out of the traversal's registers
     double *lacc = reinterpret_cast<double *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK) + tid;
-    // adjoint only: the hit chains (hit k at [k * BLOCK]), then per-wave gradient sums
-    uint32_t *lchain = reinterpret_cast<uint32_t *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK +
-                                                    sizeof(double) * 6 * BLOCK) + tid;
-    double *gw = reinterpret_cast<double *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK +
-                                            sizeof(uint32_t) * MAX_CHAIN * BLOCK + GRID_LDS) +
-                 (size_t)wv * lds_grad_doubles;
-
     // Every wave is persistent on its own and takes chunks from the work queues
     // until all are drained, with no block barrier.  Every queue walks the whole
     // batch in order, so expensive image regions spread over the grid and over
@@ -522,8 +546,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
     uint32_t cur_begin = 0, cur_end = 0;   // its chunk range
     // its ray grid: origin o0, steps su and sv, direction dd (3 floats each, a float4
     // apart) in LDS, read per patch (in registers they were spilled and reloaded)
-    float4 *grid = reinterpret_cast<float4 *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK +
-                                              (GRAD ? sizeof(uint32_t) * MAX_CHAIN * BLOCK : 0)) + 4 * wv;
+    float4 *grid = reinterpret_cast<float4 *>(smem + sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK) +
+                   4 * wv;
     float tmin2 = 0.0f;
     bool empty = true;
     #pragma unroll 1
@@ -561,7 +585,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
         int64_t p0 = kc * D.ppc, p1 = min(p0 + D.ppc, D.n_patches);
         // (patch order and costs: only in the 2-wave build, which the ordered
         // launches use, so the batch builds keep their registers)
-        constexpr bool ORDERED = !GRAD && WPE == 2;
+        constexpr bool ORDERED = WPE == 2;
         if (ORDERED && order) {
             // a captured forward plan of one patch per chunk hands out its patches
             // heaviest first, in the order its previous launch measured; any order
@@ -570,16 +594,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
             p1 = p0 < D.n_patches ? p0 + 1 : p0;
         }
         const int B = D.bounces;
-        const int KD = GRAD ? 0 : D.n_diffuse;          // diffuse rays per emitting hit
+        const int KD = D.n_diffuse;                     // diffuse rays per emitting hit
         const int R = B + 1 + B * KD;                   // recorded rays per pixel
         const float4 SRP_GLOBAL *dset = (const float4 SRP_GLOBAL *)D.dset;   // KD directions, then their mean
         const TraceCtx TC = trace_ctx(D);
-
-        const int gK = D.n_nodes;
-        if (GRAD) {
-            for (int i = lane; i < D.grad_n; i += WAVE) gw[i] = 0.0;
-            wave_lds_fence();
-        }
 
         // Rasterised evaluations: the hit masks of the chunk's patches (lane i: patch
         // p0 + i); patches without a hit get their zero sums here, one per lane,
@@ -589,7 +607,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
         if (seen) {
             const int64_t mp = p0 + lane;
             if (mp < p1) hits = ((const uint64_t SRP_GLOBAL *)D.vis_mask)[mp];
-            if (GRAD || KD == 0) {
+            if (KD == 0) {
                 visit = __ballot(hits != 0);
                 if (mp < p1 && hits == 0) {
                     const PatchOut none = {};
@@ -600,9 +618,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
         }
 
         if (p1 - p0 < 64) visit &= (1ull << (int)(p1 - p0)) - 1ull;   // (p0 < p1 <= p0 + MAX_PPC)
-        uint2 next = make_uint2(0, 0);   // the next visited patch's first hits, read one patch
-                                         // ahead (the adjoint has no registers for it)
-        if (!GRAD && seen && visit)
+        uint2 next = make_uint2(0, 0);   // the next visited patch's first hits, read one patch ahead
+        if (seen && visit)
             next = ((const uint2 SRP_GLOBAL *)D.vis)[(p0 + __ffsll((unsigned long long)visit) - 1) * WAVE + lane];
         #pragma unroll 1
         while (visit) {
@@ -611,13 +628,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
             // chunking or on which wave runs it
             const int64_t pt = p0 + __ffsll((unsigned long long)visit) - 1;
             visit &= visit - 1;
-            uint2 first = next;
-            if (!GRAD && seen && visit)
+            const uint2 first = next;
+            if (seen && visit)
                 next = ((const uint2 SRP_GLOBAL *)D.vis)[(p0 + __ffsll((unsigned long long)visit) - 1) * WAVE + lane];
             const int tile = (int)(pt >> 2), q = (int)(pt & 3);
             const int px = (tile % D.tiles_x) * TILE + (q & 1) * PATCH + (lane & 7);
             const int py = (tile / D.tiles_x) * TILE + (q >> 1) * PATCH + (lane >> 3);
-            if (GRAD && seen) first = ((const uint2 SRP_GLOBAL *)D.vis)[pt * WAVE + lane];
             const uint64_t clock0 = (ORDERED && cost) ? wall_clock64() : 0;
             for (int k = 0; k < 6; ++k) lacc[k * BLOCK] = 0.0;
             // hit counts packed in 10-bit fields (primary hits, specular secondary rays and
@@ -635,7 +651,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                 int K = 0;
                 const float4 g3 = grid[3];
                 float d[3] = {g3.x, g3.y, g3.z}, w = 1.0f;   // the current ray's direction and weight
-                bool cont = false;                              // the last chain hit spawned a specular ray
                 uint32_t emitted = 0;                           // generations whose hit emitted a fan
                 if (inside && D.hit_ids) {   // rays that are not traced or miss stay "no hit"
                     for (int s = 0; s < R; ++s) {
@@ -674,7 +689,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                         float n[3], cth, rs, rd;
                         int32_t id;
                         const bool flip = hit_normal(TC, D, h, d, n, cth, rs, rd, id);
-                        const bool emit = !GRAD && KD > 0 && gen < B && rd > 0.0f;
+                        const bool emit = KD > 0 && gen < B && rd > 0.0f;
                         const bool spec = gen < B && rs > 0.0f;
                         const float a = w * (1.0f - rs);
                         float f[3], x[3];
@@ -701,9 +716,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                                 (int8_t)(planar_node(D, h.inst) ? h.inst : -1);
                             emitted |= 1u << gen;
                         }
-                        if (GRAD) lchain[K * BLOCK] = (uint32_t)h.tri | (flip ? CHAIN_FLIP : 0u);
-                        ++K;
-                        cont = false;
+                        if (D.chain)   // (hit number gen of the chain)
+                            ((uint32_t SRP_GLOBAL *)D.chain)[(pt * (B + 1) + gen) * WAVE + lane] =
+                                (uint32_t)h.tri | (flip ? CHAIN_FLIP : 0u);
+                        K = gen + 1;
                         if (!spec) break;
                         for (int k = 0; k < 3; ++k) {
                             o[k] = x[k];
@@ -714,122 +730,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                         excl = id;
                         skip = planar_node(D, h.inst) ? h.inst : -1;
                         ++gen;
-                        cont = true;
                         hcnt += 1u << 10;
                     }
                 }
-                if (!GRAD && KD > 0) {
+                if (D.chain && K <= B)   // ends the pixel's chain
+                    ((uint32_t SRP_GLOBAL *)D.chain)[(pt * (B + 1) + K) * WAVE + lane] = CHAIN_END;
+                if (KD > 0) {
                     // which slots of the patch's emitter region hold records, per generation
                     #pragma unroll
                     for (int g = 0; g < SRP_MAX_BOUNCES; ++g) {
                         if (g >= B) break;
                         em[g] = __ballot((emitted >> g) & 1u);
                         if (lane == 0) ((uint64_t SRP_GLOBAL *)D.emit_mask)[(size_t)pt * B + g] = em[g];
-                    }
-                }
-                if (GRAD) {
-                    // Reverse sweep over the chain at fixed visibility.
-                    //   A  = d(sum of later contributions)/d(incoming direction)   (3x3)
-                    //   Tn = later contributions divided by the weight after this hit
-                    const int Kmax = wave_max_i32(K);
-                    float A[9], Tn[3] = {0, 0, 0};
-                    float n0[3] = {0, 0, 0}, c0 = 1.0f;   // the primary hit's normal and cosine (DIR)
-                    m3_zero(A);
-                    for (int k = Kmax - 1; k >= 0; --k) {
-                        const bool act = k < K;
-                        float Hm[9], gmat[6];
-                        int node = 0, mat = 0;
-                        if (act) {
-                            // hit k's normal exactly as the forward pass computed it
-                            // the triangle record in one round trip, then its instance's
-                            // rotation and its material together
-                            const uint32_t ew = lchain[k * BLOCK];
-                            const float4 SRP_GLOBAL *tq = (const float4 SRP_GLOBAL *)(TC.tris + (ew & ~CHAIN_FLIP));
-                            const float4 T0 = tq[0], T1 = tq[1], T2 = tq[2];
-                            const int tnode = f2i(T2.w), tmat = f2i(T1.w);
-                            const Inst SRP_GLOBAL &I = TC.inst[tnode];
-                            const float4 Ra = *(const float4 SRP_GLOBAL *)&I.R[0], Rb = *(const float4 SRP_GLOBAL *)&I.R[4];
-                            const float R8 = I.R[8];
-                            const float2 rm = ((const float2 SRP_GLOBAL *)D.mats)[tmat];
-                            const float IR[9] = {Ra.x, Ra.y, Ra.z, Ra.w, Rb.x, Rb.y, Rb.z, Rb.w, R8};
-                            float e1[3] = {T1.x - T0.x, T1.y - T0.y, T1.z - T0.z};
-                            float e2[3] = {T2.x - T0.x, T2.y - T0.y, T2.z - T0.z};
-                            float nl[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
-                                           e1[0] * e2[1] - e1[1] * e2[0]};
-                            float n[3];
-                            for (int i = 0; i < 3; ++i)
-                                n[i] = IR[3 * i] * nl[0] + IR[3 * i + 1] * nl[1] + IR[3 * i + 2] * nl[2];
-                            float inv = rsqrtf(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-                            if (ew & CHAIN_FLIP) inv = -inv;
-                            for (int i = 0; i < 3; ++i) n[i] *= inv;
-                            const float rs = rm.x, rd = rm.y;
-                            // (d, w) hold the ray after hit k when hit k spawned one: undo the
-                            // reflection and the weight factor to get hit k's incoming ray
-                            if (k < K - 1 || cont) {
-                                const float dn = n[0] * d[0] + n[1] * d[1] + n[2] * d[2];
-                                for (int i = 0; i < 3; ++i) d[i] = fmaf(-2.0f * dn, n[i], d[i]);
-                                w = w / rs;
-                            }
-                            const float cc = -(n[0] * d[0] + n[1] * d[1] + n[2] * d[2]);
-                            const float sc = rs * cc + rd * (1.0f / 3.0f);
-                            if (DIR && k == 0) {
-                                for (int i = 0; i < 3; ++i) n0[i] = n[i];
-                                c0 = cc;
-                            }
-                            // material terms
-                            for (int i = 0; i < 3; ++i) {
-                                gmat[i] = w * (-d[i] - 2.0f * cc * n[i] + Tn[i]);
-                                gmat[3 + i] = w * (-2.0f / 3.0f) * n[i];
-                            }
-                            // G = dF/dn (explicit) + A (2c I - 2 n d^T)
-                            float G[9];
-                            for (int i = 0; i < 3; ++i)
-                                for (int j = 0; j < 3; ++j) {
-                                    float e = w * (2.0f * rs * n[i] * d[j] - (i == j ? 2.0f * sc : 0.0f));
-                                    float an = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
-                                    e += 2.0f * cc * A[3 * i + j] - 2.0f * an * d[j];
-                                    G[3 * i + j] = e;
-                                }
-                            if (k == 0) {
-                                // the primary ray keeps its share of the triangle's visible surface,
-                                // whose projected area scales with c0 = -n0.d: the whole chain's
-                                // contribution S (per unit weight) adds dF/dn0 = -S d^T / c0
-                                float S[3];
-                                for (int i = 0; i < 3; ++i) S[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
-                                const float ws = w / cc;
-                                for (int i = 0; i < 3; ++i)
-                                    for (int j = 0; j < 3; ++j) G[3 * i + j] -= ws * S[i] * d[j];
-                            }
-                            // H = -G [n]x
-                            for (int i = 0; i < 3; ++i) {
-                                const float g0 = G[3 * i], g1 = G[3 * i + 1], g2 = G[3 * i + 2];
-                                Hm[3 * i + 0] = -(g1 * n[2] - g2 * n[1]);
-                                Hm[3 * i + 1] = -(g2 * n[0] - g0 * n[2]);
-                                Hm[3 * i + 2] = -(g0 * n[1] - g1 * n[0]);
-                            }
-                            // A <- dF_k/dd + A (I - 2 n n^T);  Tn <- f_k + rs Tn
-                            float An[3];
-                            for (int i = 0; i < 3; ++i) An[i] = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
-                            for (int i = 0; i < 3; ++i)
-                                for (int j = 0; j < 3; ++j)
-                                    A[3 * i + j] = A[3 * i + j] - 2.0f * An[i] * n[j] +
-                                                   w * ((i == j ? 1.0f - rs : 0.0f) + 2.0f * rs * n[i] * n[j]);
-                            for (int i = 0; i < 3; ++i) Tn[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
-                            node = tnode;
-                            mat = tmat;
-                        }
-                        wave_scatter_add<9>(gw, node, act, Hm, 9);
-                        wave_scatter_add<6>(gw + 9 * gK, mat, act, gmat, 6);
-                    }
-                    // Photon-direction Jacobian of the ray's whole chain, each primary ray
-                    // keeping its triangle and its share of that triangle's visible area
-                    // (the share's projected area scales with c = -n0.d):
-                    //   dF/dd = A - S n0^T / c0,  S = chain contribution per unit weight (Tn)
-                    if (DIR && (D.flags & SRP_F_GRAD_DIR)) {
-                        float Jd[9];
-                        for (int i = 0; i < 3; ++i)
-                            for (int j = 0; j < 3; ++j) Jd[3 * i + j] = A[3 * i + j] - Tn[i] * n0[j] / c0;
-                        wave_scatter_add<9>(gw + 9 * gK + 6 * D.n_mats, 0, K > 0, Jd, 9);
                     }
                 }
             }
@@ -849,12 +761,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                     counts[2 * t + 1] = ntri;
                 }
             }
-            if (!GRAD && KD > 0 && fans_inline) {
+            if (KD > 0 && fans_inline) {
                 // the patch's fans right away, from the records its lanes just wrote
                 __threadfence_block();
                 fan_passes<COUNT>(D, TC, pt, em[0], em[1], em[2], em[3], 0, 1, tmin2, stack, lacc, lane, fan_out,
                                   fan_counts);
-            } else if (!GRAD && KD > 0 && fan_units) {
+            } else if (KD > 0 && fan_units) {
                 // a fan launch follows: list the patch's non-empty fan passes as its
                 // work units (one pass each), and write the empty passes' zero
                 // partials here, as a pass with no task writes them
@@ -884,14 +796,145 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                 ((uint32_t SRP_GLOBAL *)cost)[D.patch_base + pt] = dt < 0xFFFFFFFFull ? (uint32_t)dt : 0xFFFFFFFFu;
             }
         }
-        if (GRAD) {
-            wave_lds_fence();
-            double SRP_GLOBAL *dst = (double SRP_GLOBAL *)(D.grad_part + (size_t)kc * D.grad_n);
-            for (int i = lane; i < D.grad_n; i += WAVE) dst[i] = gw[i];
-        }
     }
 }
 
+// The adjoint of the traced hit chains.  One wave per gradient group (a fixed
+// run of an evaluation's patches), one lane per pixel: each lane walks its
+// chain forward to the last ray, then back at fixed visibility, and the wave
+// adds the lanes' terms into its FP64 sums per node and material.  It traces
+// nothing, so its groups cost alike, while a launch that traced and
+// differentiated a group in one wave ended on a few groups of expensive rays
+// (12 % of its wave slots filled over an adjoint batch of the 1M-triangle
+// craft, 11 % over eight evaluations at 512^2).  Measured, both in one kernel
+// and now: 8 x 2048^2 of 1M triangles 2.62 -> 1.48 ms, the autograd step of 8 x 512^2 1.21 ->
+// 0.83, 64 x 1024^2 of 50k (many groups per wave) 3.23 -> 3.29.
+template <bool DIR>
+__global__ __launch_bounds__(BLOCK) void k_adjoint(const EvalDesc *__restrict__ descs, int first_eval,
+                                                   const PatchOut *__restrict__ patches, int lds_grad_doubles) {
+    extern __shared__ char smem[];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
+    double *gw = reinterpret_cast<double *>(smem) + (size_t)wv * lds_grad_doubles;
+    const EvalDesc &D = descs[first_eval + (int)blockIdx.y];
+    const int64_t kc = (int64_t)blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane(wv);
+    if (kc >= D.n_groups) return;   // (no block barrier below)
+    for (int i = lane; i < D.grad_n; i += WAVE) gw[i] = 0.0;
+    wave_lds_fence();
+    const TraceCtx TC = trace_ctx(D);
+    const int B = D.bounces, gK = D.n_nodes;
+    const int64_t p0 = kc * D.group, p1 = min(p0 + D.group, D.n_patches);
+    // the group's patches with hits (at most MAX_PPC patches: lane i looks at patch p0 + i)
+    uint64_t visit = __ballot(p0 + lane < p1 && patches[D.patch_base + min(p0 + lane, p1 - 1)].hits != 0);
+    #pragma unroll 1
+    while (visit) {
+        const int64_t pt = p0 + __ffsll((unsigned long long)visit) - 1;
+        visit &= visit - 1;
+        const uint32_t SRP_GLOBAL *chain = (const uint32_t SRP_GLOBAL *)D.chain + pt * (B + 1) * WAVE + lane;
+        int K = 0;
+        for (; K <= B; ++K)
+            if (chain[K * WAVE] == CHAIN_END) break;
+        const int Kmax = wave_max_i32(K);
+        // the ray after the last hit, as the trace kernel formed it
+        float d[3] = {(float)D.d[0], (float)D.d[1], (float)D.d[2]}, w = 1.0f;
+        bool cont = false;   // the last chain hit spawned a specular ray
+        ChainHit last = {};
+        for (int k = 0; k < K; ++k) {
+            last = chain_hit(TC, D, chain[k * WAVE]);
+            const float cth = -(last.n[0] * d[0] + last.n[1] * d[1] + last.n[2] * d[2]);
+            cont = k < B && last.rs > 0.0f;
+            if (!cont) break;
+            for (int i = 0; i < 3; ++i) d[i] = fmaf(2.0f * cth, last.n[i], d[i]);
+            w *= last.rs;
+        }
+            // Reverse sweep over the chain at fixed visibility.
+            //   A  = d(sum of later contributions)/d(incoming direction)   (3x3)
+            //   Tn = later contributions divided by the weight after this hit
+            float A[9], Tn[3] = {0, 0, 0};
+            float n0[3] = {0, 0, 0}, c0 = 1.0f;   // the primary hit's normal and cosine (DIR)
+            m3_zero(A);
+            for (int k = Kmax - 1; k >= 0; --k) {
+                const bool act = k < K;
+                float Hm[9], gmat[6];
+                int node = 0, mat = 0;
+                if (act) {
+                    // hit k's normal exactly as the forward pass computed it
+                    ChainHit C = last;
+                    if (k < K - 1) C = chain_hit(TC, D, chain[k * WAVE]);
+                    const int tnode = C.node, tmat = C.mat;
+                    const float n[3] = {C.n[0], C.n[1], C.n[2]}, rs = C.rs, rd = C.rd;
+                    // (d, w) hold the ray after hit k when hit k spawned one: undo the
+                    // reflection and the weight factor to get hit k's incoming ray
+                    if (k < K - 1 || cont) {
+                        const float dn = n[0] * d[0] + n[1] * d[1] + n[2] * d[2];
+                        for (int i = 0; i < 3; ++i) d[i] = fmaf(-2.0f * dn, n[i], d[i]);
+                        w = w / rs;
+                    }
+                    const float cc = -(n[0] * d[0] + n[1] * d[1] + n[2] * d[2]);
+                    const float sc = rs * cc + rd * (1.0f / 3.0f);
+                    if (DIR && k == 0) {
+                        for (int i = 0; i < 3; ++i) n0[i] = n[i];
+                        c0 = cc;
+                    }
+                    // material terms
+                    for (int i = 0; i < 3; ++i) {
+                        gmat[i] = w * (-d[i] - 2.0f * cc * n[i] + Tn[i]);
+                        gmat[3 + i] = w * (-2.0f / 3.0f) * n[i];
+                    }
+                    // G = dF/dn (explicit) + A (2c I - 2 n d^T)
+                    float G[9];
+                    for (int i = 0; i < 3; ++i)
+                        for (int j = 0; j < 3; ++j) {
+                            float e = w * (2.0f * rs * n[i] * d[j] - (i == j ? 2.0f * sc : 0.0f));
+                            float an = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
+                            e += 2.0f * cc * A[3 * i + j] - 2.0f * an * d[j];
+                            G[3 * i + j] = e;
+                        }
+                    if (k == 0) {
+                        // the primary ray keeps its share of the triangle's visible surface,
+                        // whose projected area scales with c0 = -n0.d: the whole chain's
+                        // contribution S (per unit weight) adds dF/dn0 = -S d^T / c0
+                        float S[3];
+                        for (int i = 0; i < 3; ++i) S[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
+                        const float ws = w / cc;
+                        for (int i = 0; i < 3; ++i)
+                            for (int j = 0; j < 3; ++j) G[3 * i + j] -= ws * S[i] * d[j];
+                    }
+                    // H = -G [n]x
+                    for (int i = 0; i < 3; ++i) {
+                        const float g0 = G[3 * i], g1 = G[3 * i + 1], g2 = G[3 * i + 2];
+                        Hm[3 * i + 0] = -(g1 * n[2] - g2 * n[1]);
+                        Hm[3 * i + 1] = -(g2 * n[0] - g0 * n[2]);
+                        Hm[3 * i + 2] = -(g0 * n[1] - g1 * n[0]);
+                    }
+                    // A <- dF_k/dd + A (I - 2 n n^T);  Tn <- f_k + rs Tn
+                    float An[3];
+                    for (int i = 0; i < 3; ++i) An[i] = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
+                    for (int i = 0; i < 3; ++i)
+                        for (int j = 0; j < 3; ++j)
+                            A[3 * i + j] = A[3 * i + j] - 2.0f * An[i] * n[j] +
+                                           w * ((i == j ? 1.0f - rs : 0.0f) + 2.0f * rs * n[i] * n[j]);
+                    for (int i = 0; i < 3; ++i) Tn[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
+                    node = tnode;
+                    mat = tmat;
+                }
+                wave_scatter_add<9>(gw, node, act, Hm, 9);
+                wave_scatter_add<6>(gw + 9 * gK, mat, act, gmat, 6);
+            }
+            // Photon-direction Jacobian of the ray's whole chain, each primary ray
+            // keeping its triangle and its share of that triangle's visible area
+            // (the share's projected area scales with c = -n0.d):
+            //   dF/dd = A - S n0^T / c0,  S = chain contribution per unit weight (Tn)
+            if (DIR && (D.flags & SRP_F_GRAD_DIR)) {
+                float Jd[9];
+                for (int i = 0; i < 3; ++i)
+                    for (int j = 0; j < 3; ++j) Jd[3 * i + j] = A[3 * i + j] - Tn[i] * n0[j] / c0;
+                wave_scatter_add<9>(gw + 9 * gK + 6 * D.n_mats, 0, K > 0, Jd, 9);
+            }
+    }
+    wave_lds_fence();
+    double SRP_GLOBAL *dst = (double SRP_GLOBAL *)(D.grad_part + (size_t)kc * D.grad_n);
+    for (int i = lane; i < D.grad_n; i += WAVE) dst[i] = gw[i];
+}
 // Fan work of the trace kernel's recorded emitters as a separate launch, for
 // batches too small to fill the GPU with whole patches: one unit per
 // non-empty fan pass, as the trace kernel listed them (evaluation, patch,
@@ -1063,7 +1106,7 @@ __global__ __launch_bounds__(RBLOCK) void k_slices(const EvalDesc *__restrict__ 
     if (GRAD) {
         const int G = D.grad_n;
         const double *gp = D.grad_part;
-        const int64_t NC = D.n_chunks, r0 = NC * q / Q, r1 = NC * (q + 1) / Q;
+        const int64_t NC = D.n_groups, r0 = NC * q / Q, r1 = NC * (q + 1) / Q;
         const int P = (G > 0 && G <= RBLOCK) ? RBLOCK / G : 1;
         __shared__ double sl[RBLOCK];
         auto slice_sum = [&](int i, int64_t a0, int64_t a1) {
@@ -1253,47 +1296,51 @@ int launch_window(const EvalDesc *d_desc, int n_evals, int blocks_x, uint64_t *d
     return check(hipGetLastError());
 }
 
-size_t trace_lds_bytes(bool grad, int lds_grad_doubles) {
-    return sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK +
-           GRID_LDS + (grad ? sizeof(uint32_t) * MAX_CHAIN * BLOCK + sizeof(double) * (BLOCK / 64) * lds_grad_doubles : 0);
-}
+size_t trace_lds_bytes() { return sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(double) * 6 * BLOCK + GRID_LDS; }
 
 int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_evals, const uint64_t *d_win,
                  int64_t total_chunks, uint32_t *d_queue, uint32_t *d_spill, PatchOut *d_chunks,
-                 uint64_t *d_counts, bool count, bool grad, bool dir, int grid_blocks, int lds_grad_doubles,
-                 PatchOut *d_fan_out, uint64_t *d_fan_counts, bool fans_inline_, int4 *d_fan_units,
-                 int blocks_per_cu, const uint32_t *d_order, uint32_t *d_cost, void *stream) {
+                 uint64_t *d_counts, bool count, int grid_blocks, PatchOut *d_fan_out, uint64_t *d_fan_counts,
+                 bool fans_inline_, int4 *d_fan_units, int blocks_per_cu, const uint32_t *d_order, uint32_t *d_cost,
+                 void *stream) {
     if (total_chunks <= 0) return 0;
-    const size_t lds = trace_lds_bytes(grad, lds_grad_doubles);
-    const int lgd = grad ? lds_grad_doubles : 0;
-    const int fans_inline = (!grad && d_fan_out && fans_inline_) ? 1 : 0;
-    int4 *fan_units = (!grad && d_fan_out && !fans_inline_) ? d_fan_units : nullptr;
+    const size_t lds = trace_lds_bytes();
+    const int fans_inline = (d_fan_out && fans_inline_) ? 1 : 0;
+    int4 *fan_units = (d_fan_out && !fans_inline_) ? d_fan_units : nullptr;
     hipStream_t s = (hipStream_t)stream;
-#define SRP_LAUNCH_TRACE(C, G, R, W)                                                                              \
-    hipLaunchKernelGGL((k_trace<C, G, R, W>), dim3(grid_blocks), dim3(BLOCK), lds, s, d_desc, d_chunk_base, n_evals, \
-                       d_win, grid_blocks, total_chunks, d_queue, d_spill, d_chunks, d_counts, lgd, fans_inline,  \
+#define SRP_LAUNCH_TRACE(C, W)                                                                                    \
+    hipLaunchKernelGGL((k_trace<C, W>), dim3(grid_blocks), dim3(BLOCK), lds, s, d_desc, d_chunk_base, n_evals,     \
+                       d_win, grid_blocks, total_chunks, d_queue, d_spill, d_chunks, d_counts, fans_inline,       \
                        d_fan_out, d_fan_counts, fan_units, d_order, d_cost)
-    // (the counting variants serve tests and the benchmark's work counts: one
-    // instantiation each; both instantiations compute the same bits)
-    const bool lean = blocks_per_cu <= 2;
-    if (count && grad && dir) SRP_LAUNCH_TRACE(true, true, true, 0);
-    else if (count && grad) SRP_LAUNCH_TRACE(true, true, false, 0);
-    else if (count) SRP_LAUNCH_TRACE(true, false, false, 0);
-    else if (grad && dir && lean) SRP_LAUNCH_TRACE(false, true, true, 2);
-    else if (grad && dir) SRP_LAUNCH_TRACE(false, true, true, 0);
-    else if (grad && lean) SRP_LAUNCH_TRACE(false, true, false, 2);
-    else if (grad) SRP_LAUNCH_TRACE(false, true, false, 0);
-    else if (lean) SRP_LAUNCH_TRACE(false, false, false, 2);
-    else SRP_LAUNCH_TRACE(false, false, false, 0);
+    // (the counting variant serves tests and the benchmark's work counts: one
+    // instantiation; both instantiations compute the same bits)
+    if (count) SRP_LAUNCH_TRACE(true, 0);
+    else if (blocks_per_cu <= 2) SRP_LAUNCH_TRACE(false, 2);
+    else SRP_LAUNCH_TRACE(false, 0);
 #undef SRP_LAUNCH_TRACE
     return check(hipGetLastError());
+}
+
+int launch_adjoint(const EvalDesc *d_desc, int n_evals, int64_t max_groups, const PatchOut *d_patches, bool dir,
+                   int lds_grad_doubles, void *stream) {
+    if (n_evals <= 0 || max_groups <= 0) return 0;
+    const size_t lds = sizeof(double) * (BLOCK / WAVE) * lds_grad_doubles;
+    constexpr int ROWS = 32768;   // evaluations per launch (grid rows)
+    for (int e0 = 0; e0 < n_evals; e0 += ROWS) {
+        const dim3 grid((uint32_t)((max_groups + BLOCK / WAVE - 1) / (BLOCK / WAVE)), (uint32_t)std::min(n_evals - e0, ROWS));
+        if (dir) hipLaunchKernelGGL((k_adjoint<true>), grid, dim3(BLOCK), lds, (hipStream_t)stream, d_desc, e0, d_patches, lds_grad_doubles);
+        else hipLaunchKernelGGL((k_adjoint<false>), grid, dim3(BLOCK), lds, (hipStream_t)stream, d_desc, e0, d_patches, lds_grad_doubles);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return (int)err;
+    }
+    return 0;
 }
 
 int launch_fans(const EvalDesc *d_desc, const uint64_t *d_win, int64_t max_units, uint32_t *d_queue,
                 uint32_t *d_spill, PatchOut *d_fan_out, uint64_t *d_fan_counts, const int4 *d_fan_units, bool count,
                 int grid_blocks, void *stream) {
     if (max_units <= 0) return 0;
-    const size_t lds = trace_lds_bytes(false, 0);   // the same ring and accumulators as the forward trace
+    const size_t lds = trace_lds_bytes();   // the same ring and accumulators as the forward trace
     hipStream_t s = (hipStream_t)stream;
     if (count)
         hipLaunchKernelGGL((k_fans<true>), dim3(grid_blocks), dim3(BLOCK), lds, s, d_desc, d_win, grid_blocks,
@@ -1327,22 +1374,17 @@ int launch_reduce(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, co
     return check(hipGetLastError());
 }
 
-int trace_blocks_per_cu(bool count, bool grad, bool dir, int lds_grad_doubles) {
-    const size_t lds = trace_lds_bytes(grad, lds_grad_doubles);
+int trace_blocks_per_cu(bool count) {
+    const size_t lds = trace_lds_bytes();
     int nb = 0;
-    hipError_t e;
-    if (count && grad && dir) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<true, true, true>, BLOCK, lds);
-    else if (count && grad) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<true, true, false>, BLOCK, lds);
-    else if (count) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<true, false, false>, BLOCK, lds);
-    else if (grad && dir) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<false, true, true>, BLOCK, lds);
-    else if (grad) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<false, true, false>, BLOCK, lds);
-    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<false, false, false>, BLOCK, lds);
+    hipError_t e = count ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<true, 0>, BLOCK, lds)
+                         : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<false, 0>, BLOCK, lds);
     if (e != hipSuccess || nb < 1) nb = 1;
     return nb;
 }
 
 int fan_blocks_per_cu(bool count) {
-    const size_t lds = trace_lds_bytes(false, 0);
+    const size_t lds = trace_lds_bytes();
     int nb = 0;
     hipError_t e = count ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fans<true>, BLOCK, lds)
                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fans<false>, BLOCK, lds);

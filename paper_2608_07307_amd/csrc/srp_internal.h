@@ -45,7 +45,7 @@ constexpr int TLAS_MAX_DEPTH = 7;           // <= 128 instances, median split (b
 constexpr int BLOCK = 256;                  // threads per block of the trace kernel (4 waves)
 constexpr int PATCH = 8;                    // a patch is PATCH x PATCH pixels: one ray per lane of a wave
 constexpr int TILE = 16;                    // patches are numbered by 16x16 tile (row-major), 4 per tile
-constexpr int MAX_PPC = 64;                 // patches per chunk (one wave's work item) at most
+constexpr int MAX_PPC = 64;                 // patches per chunk or gradient group (one wave's work item) at most
 constexpr int MAX_GRAD_SLOTS = 960;         // doubles per wave for gradient partials (LDS <= 64 KB)
 
 #define SRP_HD __host__ __device__
@@ -213,9 +213,9 @@ struct alignas(64) EvalDesc {
     uint32_t flags;
     int32_t tiles_x;        // 16-pixel tile columns
     int32_t ppc;            // patches per chunk
-    int32_t grad_n;         // doubles per chunk gradient partial (0 = no gradient)
-    int64_t chunk_base;     // first chunk of this evaluation
-    int64_t n_chunks;
+    int32_t grad_n;         // doubles per group gradient partial (0 = no gradient)
+    uint32_t *chain;        // adjoint: the pixels' hit chains, n_patches x (bounces + 1) x 64 words, or null
+    int64_t n_groups;       // adjoint: gradient groups
     int64_t patch_base;     // first patch of this evaluation (partial sums are per patch)
     int64_t n_patches;      // 4 * tiles_x * tiles_y
     int32_t tiles_y;        // 16-pixel tile rows
@@ -223,7 +223,7 @@ struct alignas(64) EvalDesc {
     // optional outputs
     int32_t *hit_ids;       // N*N*R (R = B+1 + B*n_diffuse) or null
     float *hit_t;
-    double *grad_part;      // n_chunks x grad_n (gradient partials)
+    double *grad_part;      // n_groups x grad_n (gradient partials)
     double *grad_out;       // 3*(2M+J) final gradient or null
     const float *dset;      // n_diffuse > 0: the diffuse set, 4 floats per ray (x, y, z, 0), then its mean
     FanRec *emit;           // n_diffuse > 0, forward: emitter records, n_patches x bounces x 64, then as
@@ -243,6 +243,7 @@ struct alignas(64) EvalDesc {
     const int32_t *leaf_of; // T: leaf-order index of an original triangle index
     const ArtNode *art;     // K tree nodes
     PrimaryEval *prim;      // the image of this evaluation's instances: a PrimaryEval, then K PrimaryInst
+    int32_t group;          // patches per gradient group
 };
 
 // The host writes these records and the kernels read them: both compilation
@@ -274,8 +275,8 @@ static_assert(offsetof(EvalDesc, flags) == 216, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, tiles_x) == 220, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, ppc) == 224, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, grad_n) == 228, "EvalDesc layout");
-static_assert(offsetof(EvalDesc, chunk_base) == 232, "EvalDesc layout");
-static_assert(offsetof(EvalDesc, n_chunks) == 240, "EvalDesc layout");
+static_assert(offsetof(EvalDesc, chain) == 232, "EvalDesc layout");
+static_assert(offsetof(EvalDesc, n_groups) == 240, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, patch_base) == 248, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, n_patches) == 256, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, tiles_y) == 264, "EvalDesc layout");
@@ -357,9 +358,14 @@ int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, i
 // patch's trace time (constant-rate clock ticks).
 int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_evals,
                  const uint64_t *d_win, int64_t total_chunks, uint32_t *d_queue, uint32_t *d_spill,
-                 PatchOut *d_patches, uint64_t *d_counts, bool count, bool grad, bool dir, int grid_blocks,
-                 int lds_grad_doubles, PatchOut *d_fan_out, uint64_t *d_fan_counts, bool fans_inline,
-                 int4 *d_fan_units, int blocks_per_cu, const uint32_t *d_order, uint32_t *d_cost, void *stream);
+                 PatchOut *d_patches, uint64_t *d_counts, bool count, int grid_blocks, PatchOut *d_fan_out,
+                 uint64_t *d_fan_counts, bool fans_inline, int4 *d_fan_units, int blocks_per_cu,
+                 const uint32_t *d_order, uint32_t *d_cost, void *stream);
+// Gradient partials of every group from the chains and hit counts that the
+// trace kernel wrote (max_groups: the most groups of any evaluation;
+// lds_grad_doubles: the largest grad_n).
+int launch_adjoint(const EvalDesc *d_desc, int n_evals, int64_t max_groups, const PatchOut *d_patches, bool dir,
+                   int lds_grad_doubles, void *stream);
 // Diffuse fans of the recorded emitters: one work unit per non-empty fan pass,
 // as the trace kernel listed them in d_fan_units (at most max_units); uses the
 // second set of queue counters and the same spill area as the trace kernel.
@@ -376,7 +382,7 @@ int launch_reduce(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, co
                   bool grad, const uint32_t *d_slice_eval, int64_t total_slices, void *d_out, uint32_t *d_order,
                   const uint32_t *d_cost, uint32_t *d_order_launch, void *stream);
 // Resident blocks per compute unit of the trace kernel variant.
-int trace_blocks_per_cu(bool count, bool grad, bool dir, int lds_grad_doubles);
+int trace_blocks_per_cu(bool count);
 // Resident blocks per compute unit of the fan kernel variant.
 int fan_blocks_per_cu(bool count);
 
