@@ -324,7 +324,7 @@ struct Layout {
     int grid = 1, fan_grid = 0, wb = 1;
     // primary hits by rasterisation (k_primary): the items it serves, their first
     // patch in its buffers, its tile and the most tiles of any item
-    bool allow_vis = true;
+    bool roomy = true;   // buffers that only buy speed are allowed: rasterised hits, unit lists of big fan launches
     std::vector<char> item_vis;
     std::vector<int64_t> vis_base;
     std::vector<size_t> prim_off;
@@ -437,7 +437,7 @@ constexpr int64_t RASTER_MIN_PATCHES = 16384, RASTER_BIG_PATCHES = 131072;
 int raster_tile(int64_t patches) { return patches >= RASTER_BIG_PATCHES ? 16 : 8; }
 
 int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule force, Layout *Lp,
-                 bool allow_vis = true) {
+                 bool roomy = true) {
     Layout &L = *Lp;
     L = Layout();
     L.n = n;
@@ -486,18 +486,29 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     }
     L.chunk_base[n] = L.total_chunks;
     // diffuse fans (forward only; emitters are chain hits of generation < bounces).
-    // Many patches with fans: the trace kernel traces each patch's fans right after
-    // its chains.  Few: the trace kernel lists every patch's non-empty fan passes and
-    // a fan kernel follows with one unit per listed pass, so that a small batch
-    // still fills the GPU and a heavy patch's passes run side by side.  Both give
-    // the same bits.
-    int64_t fan_patches = 0;
+    // Either the trace kernel traces each patch's fans right after its chains, or it
+    // lists every patch's non-empty fan passes and a fan kernel follows with one unit
+    // per listed pass, so that a small batch still fills the GPU and a heavy patch's
+    // passes run side by side.  Both give the same bits.  Measured inline / separate,
+    // in us, at B x K = 5, 16, 32 and 62 fan rays per pixel: 150 evaluations of the 50k
+    // craft at 100^2 669 / 623, 1283 / 981, 1699 / 1203, 3015 / 1692, 64 at 256^2 882 / 1015,
+    // 1701 / 1691, 2388 / 1977, 4043 / 2999, 300 at 256^2 3080 / 3613, -, 9431 / 7933, -; the
+    // 16-triangle box-wing at 100^2 304 / 345, 427 / 428, 493 / 445, 693 / 583, at 256^2 314 / 602,
+    // 516 / 798, 596 / 829, 926 / 1115; a 5,120-triangle sphere at 256^2 1748 / 2154, 4088 / 4602,
+    // 4145 / 4652, 7551 / 8080.  A separate launch costs about 4 ns per patch and a microsecond per
+    // pass; inline, a launch ends on a few patches of up to 1.7 ms each, which weighs
+    // more where a launch is small and rays are expensive.
+    int64_t fan_patches = 0, fan_rays = INT64_MAX, fan_tris = INT64_MAX;
     for (int64_t k = 0; k < n; ++k)
-        if (!grad && items[k].p.bounces > 0 && items[k].p.n_diffuse > 0)
+        if (!grad && items[k].p.bounces > 0 && items[k].p.n_diffuse > 0) {
             fan_patches += L.patch_base[k + 1] - L.patch_base[k];
+            fan_rays = std::min<int64_t>(fan_rays, (int64_t)items[k].p.bounces * items[k].p.n_diffuse);
+            fan_tris = std::min<int64_t>(fan_tris, items[k].scene->h.n_tris);
+        }
     if (fan_patches > 0) {
         const int64_t resident = (int64_t)g_ws.n_cu * fan_blocks_per_cu(L.count) * (BLOCK / 64);
-        L.fans_inline = fan_patches >= 2 * resident;
+        const bool dear = roomy && fan_rays >= 16 && (fan_tris >= 32768 || fan_patches < 8 * resident);
+        L.fans_inline = fan_patches >= 2 * resident && !dear;
     }
     // partial slots: one per pass of 64 tasks (emitter, slice of FAN_SLICE fan rays), at
     // most bounces x ceil(n_diffuse / FAN_SLICE) per patch
@@ -617,8 +628,8 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     L.item_vis.assign(n, 0);
     L.vis_base.assign(n, 0);
     L.prim_off.assign(n, 0);
-    L.allow_vis = allow_vis;
-    if (allow_vis && !L.count) {   // (a counting launch counts the traversal's tests)
+    L.roomy = roomy;
+    if (roomy && !L.count) {   // (a counting launch counts the traversal's tests)
         double ratio = 0.6;
         for (int64_t least : {RASTER_BIG_PATCHES, RASTER_MIN_PATCHES}) {
             L.vis_patches = 0;
@@ -895,8 +906,7 @@ int run_batch(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
         HIPCHK(hipStreamWaitEvent(stream, g_ws.done, 0));
     }
     rc = ws_reserve(L.dev_bytes, L.stage_bytes);   // (waits for the last batch to grow)
-    if (rc == SRP_ERR_OOM && L.vis_patches > 0) {
-        // no room for the rasterised hits: trace the primary rays
+    if (rc == SRP_ERR_OOM) {   // no room: without the buffers that only buy speed
         if ((rc = layout_build(items, n, grad, force, &L, false))) return rc;
         rc = ws_reserve(L.dev_bytes, L.stage_bytes);
     }
@@ -970,11 +980,11 @@ int plan_make(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
     PlanImpl *P = new (std::nothrow) PlanImpl();
     if (!P) return fail(SRP_ERR_OOM, "host allocation failed");
     P->bo = bo;
-    // (rasterised hits only while the plan's own buffer stays within the workspace cap and fits)
-    for (bool vis : {true, false}) {
-        if ((rc = layout_build(items, n, grad, Schedule(), &P->L, vis))) { plan_free(P); return rc; }
+    // (buffers that only buy speed only while the plan's own stays within the workspace cap and fits)
+    for (bool roomy : {true, false}) {
+        if ((rc = layout_build(items, n, grad, Schedule(), &P->L, roomy))) { plan_free(P); return rc; }
         layout_add_order(P->L);
-        const bool retry = vis && P->L.vis_patches > 0;
+        const bool retry = roomy;
         if (retry && P->L.dev_bytes > WORKSPACE_CAP) continue;
         if (hipMalloc(&P->d_buf, std::max<size_t>(P->L.dev_bytes, 256)) == hipSuccess) break;
         (void)hipGetLastError();
@@ -1035,7 +1045,7 @@ int plan_refill(PlanImpl *P, const srp_batch_item *items, int64_t n, bool *compa
     int rc = check_items(items, n, P->L.grad, P->bo);
     if (rc) return rc;
     Layout L2;
-    if ((rc = layout_build(items, n, P->L.grad, P->L.sch, &L2, P->L.allow_vis))) return rc;
+    if ((rc = layout_build(items, n, P->L.grad, P->L.sch, &L2, P->L.roomy))) return rc;
     if (P->L.ordered) layout_add_order(L2);
     const Layout &L = P->L;
     if (L2.n != L.n || L2.stage_bytes != L.stage_bytes || L2.dev_bytes > L.dev_bytes || L2.grid != L.grid ||
@@ -1339,8 +1349,8 @@ int srp_eval_batch_noalloc(const srp_batch_item *items, int64_t n_items, srp_res
     if (rc) return rc;
     Layout L;
     if ((rc = layout_build(items, n_items, false, Schedule(), &L))) return rc;
-    // (rasterised hits only where they fit beside the whole grid's stacks)
-    if (L.vis_patches > 0 && L.dev_bytes > NOALLOC_SCRATCH_BYTES &&
+    // (buffers that only buy speed only where they fit beside the whole grid's stacks)
+    if (L.dev_bytes > NOALLOC_SCRATCH_BYTES &&
         (rc = layout_build(items, n_items, false, Schedule(), &L, false)))
         return rc;
     if ((rc = layout_fit(&L, NOALLOC_SCRATCH_BYTES))) return rc;
