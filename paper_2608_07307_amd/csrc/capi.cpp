@@ -458,14 +458,17 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         L.max_wpts = std::max<int64_t>(L.max_wpts, (int64_t)it.scene->h.wpts.size());
     }
     L.patch_base[n] = L.total_patches;
-    // the reduction's first stage: range sums of about 1,024 patches each (at most
-    // MAX_SLICES), a function of the item's own size, so an item's results do not
-    // depend on its batch
+    // the reduction's first stage: range sums of about 1,024 partials each, patches
+    // and fan passes (at most MAX_SLICES), a function of the item's own size, so an
+    // item's results do not depend on its batch.  (By patches alone, the 16,384 fan
+    // passes of one evaluation at 256^2, B = 2, K = 16 were one block's: 27 us, now 8.)
     L.n_slices.assign(n, 0);
     L.slice_base.assign(n + 1, 0);
     for (int64_t k = 0; k < n; ++k) {
+        const srp_eval_params &p = items[k].p;
         const int64_t np = L.patch_base[k + 1] - L.patch_base[k];
-        L.n_slices[k] = (int)std::min<int64_t>(MAX_SLICES, std::max<int64_t>(1, np / 1024));
+        const int64_t nf = grad ? 0 : np * p.bounces * ((p.n_diffuse + FAN_SLICE - 1) / FAN_SLICE);
+        L.n_slices[k] = (int)std::min<int64_t>(MAX_SLICES, std::max<int64_t>(1, (np + nf) / 1024));
         L.slice_base[k + 1] = L.slice_base[k] + L.n_slices[k];
     }
     if (L.slice_base[n] > INT32_MAX) return fail(SRP_ERR_ARG, "batch too large: more than 2^31 range sums (split it)");
