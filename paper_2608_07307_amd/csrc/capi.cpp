@@ -201,7 +201,7 @@ int ws_reserve(size_t dev_bytes, size_t host_bytes) {
         if (g_ws.h_stage) HIPCHK(hipHostFree(g_ws.h_stage));
         g_ws.h_stage = nullptr;
         size_t cap = std::max(host_bytes, g_ws.h_cap + g_ws.h_cap / 2);
-        if (hipHostMalloc(&g_ws.h_stage, cap, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(&g_ws.h_stage, cap, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
             g_ws.h_cap = 0;
             (void)hipGetLastError();
             return fail(SRP_ERR_OOM, "pinned staging allocation failed");
@@ -811,16 +811,25 @@ void staging_fill(const Layout &L, const srp_batch_item *items, const BatchOut &
     }
 }
 
+// Staging images up to this size are read from pinned memory by a kernel.
+constexpr size_t UPLOAD_BY_KERNEL = (size_t)64 << 10;
+
 // Upload + window + trace + reduce (+ optional result copy) on `stream`.
+// pinned: H is coherent pinned memory.
 int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const BatchOut &bo, hipStream_t stream,
-            bool profile, hipEvent_t copied = nullptr) {
+            bool profile, bool pinned, hipEvent_t copied = nullptr) {
     std::pair<hipEvent_t, hipEvent_t> whole{};
     if (profile) {
         int rc = prof_event_pair(&whole);
         if (rc) return rc;
         HIPCHK(hipEventRecord(whole.first, stream));
     }
-    HIPCHK(hipMemcpyAsync(Dv, H, copy_bytes, hipMemcpyHostToDevice, stream));
+    if (pinned && copy_bytes <= UPLOAD_BY_KERNEL) {
+        int e = launch_upload(Dv, H, copy_bytes, stream);
+        if (e) return fail(SRP_ERR_DEVICE, std::string("upload kernel: ") + hipGetErrorString((hipError_t)e));
+    } else {
+        HIPCHK(hipMemcpyAsync(Dv, H, copy_bytes, hipMemcpyHostToDevice, stream));
+    }
     if (copied) HIPCHK(hipEventRecord(copied, stream));
     if (!L.slots.empty()) {
         int e = launch_articulate(reinterpret_cast<const ArtJob *>(Dv + L.o_jobs), (int)L.slots.size(), stream);
@@ -915,7 +924,7 @@ int run_batch(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
     }
     if (rc) return rc;
     staging_fill(L, items, bo, g_ws.h_stage, g_ws.d_buf);
-    if ((rc = enqueue(L, g_ws.d_buf, g_ws.h_stage, L.stage_bytes, bo, stream, g_prof.on, g_ws.copied))) return rc;
+    if ((rc = enqueue(L, g_ws.d_buf, g_ws.h_stage, L.stage_bytes, bo, stream, g_prof.on, true, g_ws.copied))) return rc;
     HIPCHK(hipEventRecord(g_ws.done, stream));
     g_ws.pending = true;
     return SRP_OK;
@@ -1012,7 +1021,8 @@ int plan_make(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
                                             hipGetErrorString(e1 != hipSuccess ? e1 : e2));
         }
     }
-    if (hipHostMalloc(&P->h_stage, std::max<size_t>(P->L.stage_bytes, 256), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&P->h_stage, std::max<size_t>(P->L.stage_bytes, 256),
+                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
         plan_free(P);
         return fail(SRP_ERR_OOM, "plan staging allocation failed");
@@ -1028,7 +1038,7 @@ int plan_make(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
         plan_free(P);
         return rc;
     }
-    rc = enqueue(P->L, P->d_buf, P->h_stage, P->L.stage_bytes, P->bo, P->cs, false);
+    rc = enqueue(P->L, P->d_buf, P->h_stage, P->L.stage_bytes, P->bo, P->cs, false, true);
     hipGraph_t g = nullptr;
     hipError_t ee = hipStreamEndCapture(P->cs, &g);
     P->graph = g;
@@ -1131,7 +1141,7 @@ int eval_single(srp_scene *scene, const srp_eval_params *params, const double *a
     if ((rc = check_items(&it, 1, false, BatchOut()))) return rc;
     if (!scene->d_res) {
         if (hipMalloc(&scene->d_res, sizeof(srp_result)) != hipSuccess) { (void)hipGetLastError(); return fail(SRP_ERR_OOM, "result allocation failed"); }
-        if (hipHostMalloc(&scene->h_res, sizeof(srp_result), hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); return fail(SRP_ERR_OOM, "pinned result allocation failed"); }
+        if (hipHostMalloc(&scene->h_res, sizeof(srp_result), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) { (void)hipGetLastError(); return fail(SRP_ERR_OOM, "pinned result allocation failed"); }
     }
     const size_t R = (size_t)params->bounces + 1 + (size_t)params->bounces * params->n_diffuse;
     size_t nrec = (hit_ids || hit_t) ? (size_t)params->n * params->n * R : 0;
@@ -1180,8 +1190,7 @@ int eval_single(srp_scene *scene, const srp_eval_params *params, const double *a
         if (!P) {
             if ((rc = ws_wait())) return rc;
             BatchOut bo;
-            bo.d_out = scene->d_res;
-            bo.h_copy = scene->h_res;
+            bo.d_out = scene->h_res;   // (the reduction writes the pinned result itself)
             if ((rc = plan_make(&it, 1, false, bo, &P))) return rc;
             scene->eval_plans[key] = P;
         }
@@ -1361,7 +1370,7 @@ int srp_eval_batch_noalloc(const srp_batch_item *items, int64_t n_items, srp_res
         return fail(SRP_ERR_ARG, "batch too large for the fixed staging area: " + std::to_string(L.stage_bytes) +
                                      " bytes of " + std::to_string(NOALLOC_STAGE_BYTES) + " (split it)");
     staging_fill(L, items, bo, g_noalloc_stage, scr);
-    return enqueue(L, scr, g_noalloc_stage, L.stage_bytes, bo, (hipStream_t)hip_stream, false);
+    return enqueue(L, scr, g_noalloc_stage, L.stage_bytes, bo, (hipStream_t)hip_stream, false, false);
 }
 
 int srp_eval_grad_batch(const srp_batch_item *items, int64_t n_items, srp_result *out_dev, double *grad_dev,

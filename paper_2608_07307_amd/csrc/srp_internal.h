@@ -335,6 +335,8 @@ constexpr int N_QUEUES = 64;      // (one lane per counter when a wave looks at 
 constexpr int QUEUE_STRIDE = 8;   // (128-byte spacing measured the same)
 constexpr int FAN_UNITS_AT = 2 * N_QUEUES * QUEUE_STRIDE;
 constexpr int QUEUE_WORDS = FAN_UNITS_AT + 64;
+// Copies bytes (a multiple of 16) of pinned host memory to the device by a kernel.
+int launch_upload(char *dst, const char *src, size_t bytes, void *stream);
 int launch_window(const EvalDesc *d_desc, int n_evals, int blocks_x, uint64_t *d_win, uint32_t *d_queue,
                   void *stream);
 // Builds n_jobs articulation slots, one thread each (articulate.hip); the
