@@ -25,6 +25,7 @@
 //             patch, fan-pass and gradient partials in a fixed order.
 //   k_reduce  per evaluation, adds the ranges in order, scales by P * A_pix and
 //             writes the srp_result (and assembles the gradients).
+//   k_sums    k_slices and k_reduce in one, where every evaluation is one range.
 //
 // The per-pixel structure, the iterative secondary rays and the GPU-side
 // reduction follow Sec. 4.3 of the paper; the articulation follows Sec. 4.4.
@@ -1049,17 +1050,12 @@ constexpr uint32_t ORDER_EVERY = 8;   // launches of a plan per rebuild of its p
 // the evaluation (and, for gradients, on the patches per chunk), not on the
 // batch around it.
 template <bool COUNT, bool GRAD>
-__global__ __launch_bounds__(RBLOCK) void k_slices(const EvalDesc *__restrict__ descs,
-                                                const uint32_t *__restrict__ slice_eval,
-                                                const PatchOut *__restrict__ patches,
+__device__ __forceinline__ void slice_sum_block(const EvalDesc &D, int q, const PatchOut *__restrict__ patches,
                                                 const uint64_t *__restrict__ counts,
                                                 const PatchOut *__restrict__ fan_out,
                                                 const uint64_t *__restrict__ fan_counts) {
-    const int64_t b = blockIdx.x;
-    const int e = (int)slice_eval[b], tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
-    const EvalDesc &D = descs[e];
-    const int Q = D.n_slices, q = (int)(b - D.slice_base);
-    if (q < 0 || q >= Q) return;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
+    const int Q = D.n_slices;
     double f[6] = {0, 0, 0, 0, 0, 0};
     unsigned long long cn[5] = {0, 0, 0, 0, 0};
     uint32_t st = 0;
@@ -1142,6 +1138,19 @@ __global__ __launch_bounds__(RBLOCK) void k_slices(const EvalDesc *__restrict__ 
     }
 }
 
+template <bool COUNT, bool GRAD>
+__global__ __launch_bounds__(RBLOCK) void k_slices(const EvalDesc *__restrict__ descs,
+                                                const uint32_t *__restrict__ slice_eval,
+                                                const PatchOut *__restrict__ patches,
+                                                const uint64_t *__restrict__ counts,
+                                                const PatchOut *__restrict__ fan_out,
+                                                const uint64_t *__restrict__ fan_counts) {
+    const EvalDesc &D = descs[slice_eval[blockIdx.x]];
+    const int q = (int)((int64_t)blockIdx.x - D.slice_base);
+    if (q < 0 || q >= D.n_slices) return;
+    slice_sum_block<COUNT, GRAD>(D, q, patches, counts, fan_out, fan_counts);
+}
+
 // Heaviest-first patch order for the next launch of a captured forward plan
 // (run by the reduction's block of the evaluation, all RBLOCK threads): the
 // patches grouped by the bit length of their measured cost (trace time on
@@ -1177,13 +1186,10 @@ __device__ void patch_order(const EvalDesc &D, uint32_t *order_all, const uint32
 // sums likewise, then assembled per material and hinge DOF.  A captured
 // forward plan's block also orders the patches for the plan's next launch.
 template <bool COUNT, bool GRAD>
-__global__ __launch_bounds__(RBLOCK) void k_reduce(const EvalDesc *__restrict__ descs,
-                                                const uint64_t *__restrict__ win, srp_result *out,
-                                                uint32_t *order, const uint32_t *cost, uint32_t *order_launch) {
-    const int e = blockIdx.x, tid = threadIdx.x;
-    const EvalDesc &D = descs[e];
+__device__ __forceinline__ void reduce_block(const EvalDesc &D, int e, const uint64_t *W, srp_result *out,
+                                             uint32_t *order, const uint32_t *cost, uint32_t *order_launch) {
+    const int tid = threadIdx.x;
     const int Q = D.n_slices;
-    const uint64_t *W = win + (size_t)e * WIN_STRIDE;
     const double umin = dec_f64(W[0]), umax = -dec_f64(W[1]);
     const double vmin = dec_f64(W[2]), vmax = -dec_f64(W[3]);
     const double wu = umax - umin, wv = vmax - vmin;
@@ -1267,6 +1273,33 @@ __global__ __launch_bounds__(RBLOCK) void k_reduce(const EvalDesc *__restrict__ 
             for (int i = tid; i < 9; i += RBLOCK) g[6 * M + 3 * J + i] = has_dir ? scale * sg[9 * K + 6 * M + i] : 0.0;
         }
     }
+}
+
+template <bool COUNT, bool GRAD>
+__global__ __launch_bounds__(RBLOCK) void k_reduce(const EvalDesc *__restrict__ descs,
+                                                const uint64_t *__restrict__ win, srp_result *out,
+                                                uint32_t *order, const uint32_t *cost, uint32_t *order_launch) {
+    const int e = blockIdx.x;
+    reduce_block<COUNT, GRAD>(descs[e], e, win + (size_t)e * WIN_STRIDE, out, order, cost, order_launch);
+}
+
+// Both stages in one launch where every evaluation has a single range (below
+// 2,048 partials): one launch less, which is what bounds them (one box-wing
+// evaluation at 64^2 56.2 -> 54.6 us whole).  With several ranges the last block
+// to finish could add them, but the fence before it writes back the L2: 512^2
+// propagation stages 1.90 -> 1.95 ms, 900^2 187 -> 196 us.
+template <bool COUNT, bool GRAD>
+__global__ __launch_bounds__(RBLOCK) void k_sums(const EvalDesc *__restrict__ descs,
+                                              const PatchOut *__restrict__ patches,
+                                              const uint64_t *__restrict__ counts,
+                                              const PatchOut *__restrict__ fan_out,
+                                              const uint64_t *__restrict__ fan_counts, const uint64_t *__restrict__ win,
+                                              srp_result *out, uint32_t *order, const uint32_t *cost,
+                                              uint32_t *order_launch) {
+    const int e = blockIdx.x;
+    slice_sum_block<COUNT, GRAD>(descs[e], 0, patches, counts, fan_out, fan_counts);
+    __syncthreads();
+    reduce_block<COUNT, GRAD>(descs[e], e, win + (size_t)e * WIN_STRIDE, out, order, cost, order_launch);
 }
 
 int check(hipError_t e) { return e == hipSuccess ? 0 : (int)e; }
@@ -1378,6 +1411,11 @@ int launch_reduce(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, co
     srp_result *out = (srp_result *)d_out;
 #define SRP_LAUNCH_REDUCE(C, G)                                                                                 \
     do {                                                                                                        \
+        if (total_slices == n_evals) {                                                                          \
+            hipLaunchKernelGGL((k_sums<C, G>), dim3(n_evals), dim3(RBLOCK), 0, s, d_desc, d_patches, d_counts,  \
+                               d_fan_out, d_fan_counts, d_win, out, d_order, d_cost, d_order_launch);           \
+            break;                                                                                              \
+        }                                                                                                       \
         hipLaunchKernelGGL((k_slices<C, G>), dim3((uint32_t)total_slices), dim3(RBLOCK), 0, s, d_desc,          \
                            d_slice_eval, d_patches, d_counts, d_fan_out, d_fan_counts);                         \
         hipLaunchKernelGGL((k_reduce<C, G>), dim3(n_evals), dim3(RBLOCK), 0, s, d_desc, d_win, out, d_order,    \
