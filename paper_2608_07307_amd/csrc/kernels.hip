@@ -602,13 +602,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
 
         // Rasterised evaluations: the hit masks of the chunk's patches (lane i: patch
         // p0 + i); patches without a hit get their zero sums here, one per lane,
-        // and are not visited (half of a spacecraft's image is empty)
+        // and are not visited (half of a spacecraft's image is empty), unless every
+        // ray is to be recorded
         const bool seen = D.vis != nullptr && !((const PrimaryEval SRP_CONST *)D.prim)->traced;
         uint64_t hits = 0, visit = ~0ull;
         if (seen) {
             const int64_t mp = p0 + lane;
             if (mp < p1) hits = ((const uint64_t SRP_GLOBAL *)D.vis_mask)[mp];
-            if (KD == 0) {
+            if (KD == 0 && !D.hit_ids) {
                 visit = __ballot(hits != 0);
                 if (mp < p1 && hits == 0) {
                     const PatchOut none = {};

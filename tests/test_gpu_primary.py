@@ -113,3 +113,19 @@ def test_replayed_plan_with_rasterised_hits():
         torch.cuda.synchronize()
         assert got.tobytes() == srp.results_to_numpy(srp.eval_batch(e)).tobytes()
     plan.close()
+
+
+@pytest.mark.parametrize("n", [1024, 1100])
+def test_recorded_rays_of_a_rasterised_evaluation(n):
+    """One evaluation fine enough to be rasterised, with every ray recorded."""
+    import paper_2608_07307_amd as srp
+    mesh = _mesh("cluttered")
+    sc = srp.Scene(mesh)
+    sc.set_angles(np.full(mesh.n_dof, 0.4))
+    sun = np.array([0.3, -0.5, 0.8])
+    r = [srp.eval(sc, sun, n, bounces=2, count=c, record=True) for c in (False, True)]
+    assert r[0]["ids"].min() == -1 and r[0]["ids"].max() < len(mesh.tris)
+    assert np.array_equal(r[0]["ids"], r[1]["ids"]) and np.array_equal(r[0]["ts"], r[1]["ts"])
+    plain = srp.eval(sc, sun, n, bounces=2)
+    for f in FIELDS:
+        assert np.array_equal(np.asarray(r[0][f]), np.asarray(plain[f])), f
