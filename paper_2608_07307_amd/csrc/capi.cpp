@@ -377,7 +377,7 @@ int check_items(const srp_batch_item *items, int64_t n, bool grad, const BatchOu
 // to MAX_PPC patches whose partials for the evaluation fit GRAD_PART_EVAL
 // bytes.  A batch whose whole device workspace would exceed WORKSPACE_CAP
 // runs as consecutive sub-batches.
-constexpr int GRAD_GROUP_MIN = 8;
+constexpr int GRAD_GROUP_MIN = GROUP_PART;
 constexpr size_t GRAD_PART_EVAL = (size_t)8 << 20;
 constexpr size_t WORKSPACE_CAP = (size_t)16 << 30;   // of the MI355X's 288 GB: the 32,768-evaluation table at 512^2 (8.6 GB of patch partials) runs as one launch
 
@@ -872,7 +872,7 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
         if (e) return fail(SRP_ERR_DEVICE, std::string("fan kernel: ") + hipGetErrorString((hipError_t)e));
     }
     if (L.grad) {
-        e = launch_adjoint(d_desc, (int)L.n, L.max_groups, d_patches, L.dir, L.max_grad_n, stream);
+        e = launch_adjoint(d_desc, (int)L.n, L.max_groups, *std::max_element(L.group.begin(), L.group.end()), d_patches, L.dir, L.max_grad_n, stream);
         if (e) return fail(SRP_ERR_DEVICE, std::string("adjoint kernel: ") + hipGetErrorString((hipError_t)e));
     }
     if (profile) {   // the ray kernels: primary hits, trace, then fans or the adjoint

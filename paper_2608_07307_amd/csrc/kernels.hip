@@ -811,22 +811,31 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
 // craft, 11 % over eight evaluations at 512^2).  Measured, both in one kernel
 // and now: 8 x 2048^2 of 1M triangles 2.62 -> 1.48 ms, the autograd step of 8 x 512^2 1.21 ->
 // 0.83, 64 x 1024^2 of 50k (many groups per wave) 3.23 -> 3.29.
+// A group of more than GROUP_PART patches is shared by as many waves of the
+// block, each summing GROUP_PART of them, and their sums are added in order: a
+// wave of 64 patches with hits took 390 us, the whole launch for the 1M-triangle
+// craft (393 -> 251 us).  A block holds blockDim.x / 64 such parts, one when every
+// group is a single part.
 template <bool DIR>
-__global__ __launch_bounds__(BLOCK) void k_adjoint(const EvalDesc *__restrict__ descs, int first_eval,
-                                                   const PatchOut *__restrict__ patches, int lds_grad_doubles) {
+__global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(const EvalDesc *__restrict__ descs,
+                                                                            int first_eval, int block_waves,
+                                                                            const PatchOut *__restrict__ patches,
+                                                                            int lds_grad_doubles) {
     extern __shared__ char smem[];
-    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     double *gw = reinterpret_cast<double *>(smem) + (size_t)wv * lds_grad_doubles;
     const EvalDesc &D = descs[first_eval + (int)blockIdx.y];
-    const int64_t kc = (int64_t)blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane(wv);
-    if (kc >= D.n_groups) return;   // (no block barrier below)
+    const int parts = D.group / GROUP_PART, part = wv % parts;   // (powers of two; parts <= block_waves)
+    const int64_t kc = ((int64_t)blockIdx.x * block_waves + wv) / parts;
+    const bool mine = kc < D.n_groups;
     for (int i = lane; i < D.grad_n; i += WAVE) gw[i] = 0.0;
     wave_lds_fence();
     const TraceCtx TC = trace_ctx(D);
     const int B = D.bounces, gK = D.n_nodes;
-    const int64_t p0 = kc * D.group, p1 = min(p0 + D.group, D.n_patches);
-    // the group's patches with hits (at most MAX_PPC patches: lane i looks at patch p0 + i)
-    uint64_t visit = __ballot(p0 + lane < p1 && patches[D.patch_base + min(p0 + lane, p1 - 1)].hits != 0);
+    const int64_t p0 = kc * D.group + part * GROUP_PART, p1 = min(p0 + GROUP_PART, D.n_patches);
+    // the part's patches with hits (lane i looks at patch p0 + i)
+    uint64_t visit = __ballot(mine && p0 + lane < p1 &&
+                              patches[D.patch_base + max((int64_t)0, min(p0 + lane, D.n_patches - 1))].hits != 0);
     #pragma unroll 1
     while (visit) {
         const int64_t pt = p0 + __ffsll((unsigned long long)visit) - 1;
@@ -933,9 +942,15 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(const EvalDesc *__restrict__ 
                 wave_scatter_add<9>(gw + 9 * gK + 6 * D.n_mats, 0, K > 0, Jd, 9);
             }
     }
-    wave_lds_fence();
+    if (parts > 1) __syncthreads();   // (the same for the whole block)
+    else wave_lds_fence();
+    if (!mine || part != 0) return;
     double SRP_GLOBAL *dst = (double SRP_GLOBAL *)(D.grad_part + (size_t)kc * D.grad_n);
-    for (int i = lane; i < D.grad_n; i += WAVE) dst[i] = gw[i];
+    for (int i = lane; i < D.grad_n; i += WAVE) {
+        double t = gw[i];
+        for (int k = 1; k < parts; ++k) t += gw[(size_t)k * lds_grad_doubles + i];
+        dst[i] = t;
+    }
 }
 // Fan work of the trace kernel's recorded emitters as a separate launch, for
 // batches too small to fill the GPU with whole patches: one unit per
@@ -1372,15 +1387,22 @@ int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_eval
     return check(hipGetLastError());
 }
 
-int launch_adjoint(const EvalDesc *d_desc, int n_evals, int64_t max_groups, const PatchOut *d_patches, bool dir,
-                   int lds_grad_doubles, void *stream) {
+int launch_adjoint(const EvalDesc *d_desc, int n_evals, int64_t max_groups, int max_group, const PatchOut *d_patches,
+                   bool dir, int lds_grad_doubles, void *stream) {
     if (n_evals <= 0 || max_groups <= 0) return 0;
-    const size_t lds = sizeof(double) * (BLOCK / WAVE) * lds_grad_doubles;
+    const int waves = max_group / GROUP_PART;
+    if (waves < 1 || waves > MAX_PPC / GROUP_PART || (waves & (waves - 1))) return (int)hipErrorInvalidValue;
+    const size_t lds = sizeof(double) * waves * lds_grad_doubles;
     constexpr int ROWS = 32768;   // evaluations per launch (grid rows)
     for (int e0 = 0; e0 < n_evals; e0 += ROWS) {
-        const dim3 grid((uint32_t)((max_groups + BLOCK / WAVE - 1) / (BLOCK / WAVE)), (uint32_t)std::min(n_evals - e0, ROWS));
-        if (dir) hipLaunchKernelGGL((k_adjoint<true>), grid, dim3(BLOCK), lds, (hipStream_t)stream, d_desc, e0, d_patches, lds_grad_doubles);
-        else hipLaunchKernelGGL((k_adjoint<false>), grid, dim3(BLOCK), lds, (hipStream_t)stream, d_desc, e0, d_patches, lds_grad_doubles);
+        // (an evaluation's groups take at most one block each)
+        const dim3 grid((uint32_t)max_groups, (uint32_t)std::min(n_evals - e0, ROWS)), block(WAVE * waves);
+        if (dir)
+            hipLaunchKernelGGL((k_adjoint<true>), grid, block, lds, (hipStream_t)stream, d_desc, e0, waves, d_patches,
+                               lds_grad_doubles);
+        else
+            hipLaunchKernelGGL((k_adjoint<false>), grid, block, lds, (hipStream_t)stream, d_desc, e0, waves, d_patches,
+                               lds_grad_doubles);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return (int)err;
     }

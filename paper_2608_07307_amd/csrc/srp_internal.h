@@ -46,6 +46,7 @@ constexpr int BLOCK = 256;                  // threads per block of the trace ke
 constexpr int PATCH = 8;                    // a patch is PATCH x PATCH pixels: one ray per lane of a wave
 constexpr int TILE = 16;                    // patches are numbered by 16x16 tile (row-major), 4 per tile
 constexpr int MAX_PPC = 64;                 // patches per chunk or gradient group (one wave's work item) at most
+constexpr int GROUP_PART = 8;               // patches of a gradient group per wave of the adjoint kernel
 constexpr int MAX_GRAD_SLOTS = 960;         // doubles per wave for gradient partials (LDS <= 64 KB)
 
 #define SRP_HD __host__ __device__
@@ -364,10 +365,11 @@ int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_eval
                  uint64_t *d_fan_counts, bool fans_inline, int4 *d_fan_units, int blocks_per_cu,
                  const uint32_t *d_order, uint32_t *d_cost, void *stream);
 // Gradient partials of every group from the chains and hit counts that the
-// trace kernel wrote (max_groups: the most groups of any evaluation;
+// trace kernel wrote (max_groups: the most groups of any evaluation; max_group:
+// the largest group;
 // lds_grad_doubles: the largest grad_n).
-int launch_adjoint(const EvalDesc *d_desc, int n_evals, int64_t max_groups, const PatchOut *d_patches, bool dir,
-                   int lds_grad_doubles, void *stream);
+int launch_adjoint(const EvalDesc *d_desc, int n_evals, int64_t max_groups, int max_group, const PatchOut *d_patches,
+                   bool dir, int lds_grad_doubles, void *stream);
 // Diffuse fans of the recorded emitters: one work unit per non-empty fan pass,
 // as the trace kernel listed them in d_fan_units (at most max_units); uses the
 // second set of queue counters and the same spill area as the trace kernel.
