@@ -673,9 +673,11 @@ def main():
             "traffic_source": "not measured by this run: the committed counter record "
                               "profiles/k_trace_grad_traffic.json, used only while its kernel-code digest "
                               "and schedule match this run (null otherwise)",
-            "kernel": "k_trace<GRAD> (forward + adjoint)",
+            "kernel": "k_primary + k_trace + k_adjoint (forward + adjoint; HIP events around the three)",
             "work_per_launch": {"box_tests": n_box, "tri_tests": n_tri,
-                                "lane_ops": work, "ops_per_box": BOX_OPS, "ops_per_tri": TRI_OPS},
+                                "lane_ops": work, "ops_per_box": BOX_OPS, "ops_per_tri": TRI_OPS,
+                                "of": "every ray traced through the hierarchy (a counting launch on the same "
+                                      "inputs); the timed launch rasterises the primary rays' first hits instead"},
             "kernel_ms": round(kern_s * 1e3, 4),
             "forward_kernel_ms": round(fwd_ms / max(fwd_launches, 1), 4),
         },

@@ -5,8 +5,9 @@
 //             axes u, v and the photon direction d), merged across blocks with
 //             order-preserving 64-bit atomic min.
 //   k_trace   persistent: every wave takes chunks (runs of 8x8-pixel patches
-//             of one evaluation) from per-XCD work queues until none is left,
-//             with no block barrier; one ray per lane; two-level traversal (top level over
+//             of one evaluation) from 64 work queues until none is left,
+//             with no block barrier; one ray per lane; primary hits of large
+//             images read from k_primary's records; two-level traversal (top level over
 //             the kinematic-tree nodes, rigid instance transform, bottom level
 //             in rest-pose coordinates) with a per-lane stack (LDS ring, global
 //             spill); watertight FP32 triangle test; momentum law at each hit;
@@ -18,8 +19,10 @@
 //             adjoint it also records each pixel's hit chain.
 //   k_adjoint per group of patches, differentiates the recorded chains at
 //             fixed visibility.
-//   k_fans    small diffuse batches: the patches' fan passes as a separate
-//             persistent launch, each patch split into several work units.
+//   k_fans    the patches' fan passes as a separate persistent launch, each
+//             patch split into several work units, where the batch is small or
+//             its fans are dear (many directions through a large mesh).
+//   k_upload  copies a small staging image from pinned memory.
 //   k_slices  one block per range sum (up to 16 per evaluation, numbered
 //             through the batch), summing a contiguous range of its evaluation's
 //             patch, fan-pass and gradient partials in a fixed order.
