@@ -254,6 +254,18 @@ __device__ __forceinline__ bool hit_normal(const TraceCtx &TC, const EvalDesc &D
     return flip;
 }
 
+// The first hits' words of a lane's recorded chain (of B + 1 at most), read
+// together; later ones stay in memory.
+struct ChainWords {
+    uint32_t w0, w1, w2;
+    __device__ __forceinline__ uint32_t at(const uint32_t SRP_GLOBAL *chain, int k) const {
+        return k == 0 ? w0 : k == 1 ? w1 : k == 2 ? w2 : chain[k * WAVE];
+    }
+};
+__device__ __forceinline__ ChainWords chain_words(const uint32_t SRP_GLOBAL *chain, int B) {
+    return {chain[0], chain[min(1, B) * WAVE], chain[min(2, B) * WAVE]};
+}
+
 // A recorded chain hit: its normal bit for bit as hit_normal formed it, its
 // material and node.  The triangle's record in one round trip, then its
 // instance's rotation and its material together.
@@ -817,7 +829,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
 // A group of more than GROUP_PART patches is shared by as many waves of the
 // block, each summing GROUP_PART of them, and their sums are added in order: a
 // wave of 64 patches with hits took 390 us, the whole launch for the 1M-triangle
-// craft (393 -> 251 us).  A block holds blockDim.x / 64 such parts, one when every
+// craft (393 -> 251 us before the chains' words were read ahead).  A block holds blockDim.x / 64 such parts, one when every
 // group is a single part.
 template <bool DIR>
 __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(const EvalDesc *__restrict__ descs,
@@ -839,21 +851,33 @@ __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(const
     // the part's patches with hits (lane i looks at patch p0 + i)
     uint64_t visit = __ballot(mine && p0 + lane < p1 &&
                               patches[D.patch_base + max((int64_t)0, min(p0 + lane, D.n_patches - 1))].hits != 0);
+    // The first words of a patch's chains, read together and while the patch before
+    // is swept (a word past the chain's end is not used): one round trip in place of
+    // one per hit took the launch over 64 x 1024^2 at B = 2 from 629 to 572 us, 8 x
+    // 2048^2 at B = 1 from 254 to 236.  (Keeping the first two hits as well costs two
+    // of seven waves per SIMD: 611 and 284.)
+    const auto chain_of_first = [&](uint64_t patches_left) {
+        return (const uint32_t SRP_GLOBAL *)D.chain +
+               (p0 + __ffsll((unsigned long long)patches_left) - 1) * (B + 1) * WAVE + lane;
+    };
+    ChainWords next = {};
+    if (visit) next = chain_words(chain_of_first(visit), B);
     #pragma unroll 1
     while (visit) {
-        const int64_t pt = p0 + __ffsll((unsigned long long)visit) - 1;
+        const ChainWords cw = next;
+        const uint32_t SRP_GLOBAL *chain = chain_of_first(visit);
         visit &= visit - 1;
-        const uint32_t SRP_GLOBAL *chain = (const uint32_t SRP_GLOBAL *)D.chain + pt * (B + 1) * WAVE + lane;
+        if (visit) next = chain_words(chain_of_first(visit), B);
         int K = 0;
         for (; K <= B; ++K)
-            if (chain[K * WAVE] == CHAIN_END) break;
+            if (cw.at(chain, K) == CHAIN_END) break;
         const int Kmax = wave_max_i32(K);
         // the ray after the last hit, as the trace kernel formed it
         float d[3] = {(float)D.d[0], (float)D.d[1], (float)D.d[2]}, w = 1.0f;
         bool cont = false;   // the last chain hit spawned a specular ray
         ChainHit last = {};
         for (int k = 0; k < K; ++k) {
-            last = chain_hit(TC, D, chain[k * WAVE]);
+            last = chain_hit(TC, D, cw.at(chain, k));
             const float cth = -(last.n[0] * d[0] + last.n[1] * d[1] + last.n[2] * d[2]);
             cont = k < B && last.rs > 0.0f;
             if (!cont) break;
@@ -873,7 +897,7 @@ __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(const
                 if (act) {
                     // hit k's normal exactly as the forward pass computed it
                     ChainHit C = last;
-                    if (k < K - 1) C = chain_hit(TC, D, chain[k * WAVE]);
+                    if (k < K - 1) C = chain_hit(TC, D, cw.at(chain, k));
                     const int tnode = C.node, tmat = C.mat;
                     const float n[3] = {C.n[0], C.n[1], C.n[2]}, rs = C.rs, rd = C.rd;
                     // (d, w) hold the ray after hit k when hit k spawned one: undo the

@@ -38,3 +38,35 @@ def test_material_gradients_of_a_matt_body(n, nodes, bounces):
         # FP32 terms of at most a few times the largest force per hit: the rounding
         # of both evaluations and of the gradient's terms stays below 2^-20 of the force
         assert np.abs((F1 - F0) / 0.5 - g[m]).max() <= 2.0 ** -20 * 4 * max(scale, 1e-30), m
+
+
+@pytest.mark.parametrize("bounces", [2, 3, 4])
+def test_material_gradients_of_long_chains(bounces):
+    """With fixed specular fractions the paths do not depend on rho_d and the
+    force is affine in it, so the same difference is exact over chains of as
+    many hits as there are words read ahead (three) and more."""
+    import paper_2608_07307_amd as srp
+    mesh = synth.procedural_sized(3, 3000)
+    sc = srp.Scene(mesh)
+    rng = np.random.default_rng(5)
+    M = len(mesh.mats)
+    mats = np.zeros((M, 2))
+    mats[:, 0], mats[:, 1] = 0.5, 0.125
+    items = [(sc, rng.uniform(-1, 1, mesh.n_dof), srp.params(rng.normal(size=3), 300, bounces)) for _ in range(6)]
+    sc.set_materials(mats)
+    if bounces > 2:   # some chains are longer than those of one bounce less
+        fewer = [(s, a, srp.params(p.sun_dir, 300, bounces - 1)) for s, a, p in items]
+        count = [srp.results_to_numpy(srp.eval_batch(x))["n_secondary_hits"].sum() for x in (fewer, items)]
+        assert count[1] > count[0]
+    out, grad = srp.eval_grad_batch(items)
+    g = grad.cpu().numpy()[:, 3 * M:6 * M].reshape(len(items), M, 3)
+    F0 = srp.results_to_numpy(out)["force"]
+    scale = max(np.abs(F0).max(), np.abs(g).max())
+    for m in range(M):
+        moved = mats.copy()
+        moved[m, 1] = 0.375
+        sc.set_materials(moved)
+        F1 = srp.results_to_numpy(srp.eval_batch(items))["force"]
+        # FP32 rounding of the terms of up to five hits, in both forces (over the step of
+        # a fourth) and in the recovered weights: below 2^-20 of the largest value each
+        assert np.abs((F1 - F0) / 0.25 - g[:, m]).max() <= 2.0 ** -20 * 16 * scale, m
