@@ -1139,9 +1139,17 @@ int eval_single(srp_scene *scene, const srp_eval_params *params, const double *a
     if ((rc = ws_init())) return rc;
     srp_batch_item it{scene, angles, *params};
     if ((rc = check_items(&it, 1, false, BatchOut()))) return rc;
-    if (!scene->d_res) {
-        if (hipMalloc(&scene->d_res, sizeof(srp_result)) != hipSuccess) { (void)hipGetLastError(); return fail(SRP_ERR_OOM, "result allocation failed"); }
-        if (hipHostMalloc(&scene->h_res, sizeof(srp_result), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) { (void)hipGetLastError(); return fail(SRP_ERR_OOM, "pinned result allocation failed"); }
+    // (each by itself: a call after one of them failed must not launch with that one missing)
+    if (!scene->d_res && hipMalloc(&scene->d_res, sizeof(srp_result)) != hipSuccess) {
+        (void)hipGetLastError();
+        scene->d_res = nullptr;
+        return fail(SRP_ERR_OOM, "result allocation failed");
+    }
+    if (!scene->h_res &&
+        hipHostMalloc(&scene->h_res, sizeof(srp_result), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        scene->h_res = nullptr;
+        return fail(SRP_ERR_OOM, "pinned result allocation failed");
     }
     const size_t R = (size_t)params->bounces + 1 + (size_t)params->bounces * params->n_diffuse;
     size_t nrec = (hit_ids || hit_t) ? (size_t)params->n * params->n * R : 0;

@@ -1,0 +1,199 @@
+// A device for the library's host code (csrc/*.cpp) that computes nothing and
+// records what it is asked to do: the HIP calls and kernel launchers that the
+// host code uses, with allocations in host memory (so that uploaded staging
+// images can be read back), a limit on device memory, host allocations that
+// fail on request, and one record per launch.  Built into a shared library
+// together with the host sources by tests/test_host_calls.py.
+#include <sys/mman.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstring>
+#include <map>
+#include <vector>
+
+#include "host.h"
+
+using namespace srp;
+
+namespace {
+
+constexpr size_t NO_LIMIT = (size_t)1 << 60;
+std::map<void *, size_t> g_dev;   // device allocations
+size_t g_used = 0, g_limit = NO_LIMIT;
+int g_fail_host = 0;              // host allocations that fail from now on
+
+enum Kind : int64_t { UPLOAD = 1, ARTICULATE, WINDOW, PRIMARY, TRACE, FANS, ADJOINT, REDUCE };
+struct Record {
+    int64_t kind, a[7];
+};
+std::vector<Record> g_log;
+int64_t g_faults = 0;             // launches that would have touched memory they must not
+
+void note(int64_t kind, int64_t a = 0, int64_t b = 0, int64_t c = 0, int64_t d = 0, int64_t e = 0, int64_t f = 0) {
+    g_log.push_back({kind, {a, b, c, d, e, f, 0}});
+}
+
+}  // namespace
+
+extern "C" {
+
+void dev_limit(int64_t bytes) { g_limit = bytes < 0 ? NO_LIMIT : g_used + (size_t)bytes; }
+void dev_fail_host(int n) { g_fail_host = n; }
+int64_t dev_used() { return (int64_t)g_used; }
+int64_t dev_faults() { return g_faults; }
+void dev_clear() { g_log.clear(); }
+int64_t dev_log(int64_t *out, int64_t cap) {
+    const int64_t n = std::min<int64_t>(cap, (int64_t)g_log.size());
+    if (n > 0) std::memcpy(out, g_log.data(), (size_t)n * sizeof(Record));
+    return (int64_t)g_log.size();
+}
+
+hipError_t hipMalloc(void **p, size_t n) {
+    *p = nullptr;
+    if (g_used + n > g_limit) return hipErrorOutOfMemory;
+    void *m = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (m == MAP_FAILED) return hipErrorOutOfMemory;
+    g_dev[m] = n;
+    g_used += n;
+    *p = m;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    auto f = g_dev.find(p);
+    if (f != g_dev.end()) {
+        g_used -= f->second;
+        munmap(p, f->second);
+        g_dev.erase(f);
+    }
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned int) {
+    *p = nullptr;
+    if (g_fail_host > 0) {
+        --g_fail_host;
+        return hipErrorOutOfMemory;
+    }
+    *p = calloc(1, n);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipHostFree(void *p) {
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemset(void *d, int v, size_t n) {
+    std::memset(d, v, n);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) {
+    *v = 256;   // compute units
+    return hipSuccess;
+}
+const char *hipGetErrorString(hipError_t) { return "recording device"; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned int) {
+    *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned int) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) {
+    *g = nullptr;
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t, hipGraphNode_t *, char *, size_t) {
+    *e = nullptr;
+    return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) {
+    *e = nullptr;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned int) {
+    *e = nullptr;
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
+    *ms = 1.0f;
+    return hipSuccess;
+}
+
+}  // extern "C"
+
+namespace srp {
+
+int launch_upload(char *dst, const char *src, size_t bytes, void *) {
+    std::memcpy(dst, src, bytes);
+    note(UPLOAD, (int64_t)bytes);
+    return 0;
+}
+int launch_window(const EvalDesc *, int n_evals, int, uint64_t *, uint32_t *, void *) {
+    note(WINDOW, n_evals);
+    return 0;
+}
+int launch_articulate(const ArtJob *, int n_jobs, void *) {
+    note(ARTICULATE, n_jobs);
+    return 0;
+}
+// PRIMARY: evaluations, of them rasterised, tile, blocks launched
+int launch_primary(const EvalDesc *d, int n_evals, const uint64_t *, int tile, int max_tiles, void *) {
+    int64_t with = 0;
+    for (int k = 0; k < n_evals; ++k) with += d[k].vis != nullptr;
+    note(PRIMARY, n_evals, with, tile, (int64_t)max_tiles * n_evals);
+    return 0;
+}
+// TRACE: evaluations, chunks, fans traced inside, fan units listed
+int launch_trace(const EvalDesc *, const int64_t *, int n_evals, const uint64_t *, int64_t total_chunks, uint32_t *,
+                 uint32_t *, PatchOut *, uint64_t *, bool, int, PatchOut *d_fan_out, uint64_t *, bool fans_inline,
+                 int4 *d_fan_units, int, const uint32_t *, uint32_t *, void *) {
+    note(TRACE, n_evals, total_chunks, d_fan_out && fans_inline, d_fan_units != nullptr);
+    return 0;
+}
+// ADJOINT: evaluations, blocks launched
+int launch_adjoint(const EvalDesc *, int n_evals, int64_t max_groups, int, const PatchOut *, bool, int, void *) {
+    note(ADJOINT, n_evals, max_groups * n_evals);
+    return 0;
+}
+int launch_fans(const EvalDesc *, const uint64_t *, int64_t max_units, uint32_t *, uint32_t *, PatchOut *, uint64_t *,
+                const int4 *, bool, int, void *) {
+    note(FANS, max_units);
+    return 0;
+}
+// REDUCE: evaluations, range sums; a missing result buffer is a fault
+int launch_reduce(const EvalDesc *, int n_evals, const uint64_t *, const PatchOut *, const uint64_t *, const PatchOut *,
+                  const uint64_t *, bool, bool, const uint32_t *, int64_t total_slices, void *d_out, uint32_t *,
+                  const uint32_t *, uint32_t *, void *) {
+    note(REDUCE, n_evals, total_slices);
+    if (!d_out) ++g_faults;
+    return 0;
+}
+int trace_blocks_per_cu(bool) { return 4; }
+int fan_blocks_per_cu(bool) { return 4; }
+int noalloc_scratch_init() { return 0; }
+char *noalloc_scratch(int) {
+    static char *p = (char *)mmap(nullptr, NOALLOC_SCRATCH_BYTES, PROT_READ | PROT_WRITE,
+                                  MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    return p;
+}
+
+}  // namespace srp

@@ -1,0 +1,118 @@
+"""CPU checks of what the library's host code asks of the device: its sources
+(csrc/*.cpp) are built with the host compiler against a device that computes
+nothing and records every launch (tests/host_calls/recording_device.cpp), with
+a limit on its memory and allocations that fail on request."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import synth
+from paper_2608_07307_amd import _lib as L
+from paper_2608_07307_amd import _mesh_arrays, params
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2608_07307_amd", "csrc")
+DEVICE = os.path.join(ROOT, "tests", "host_calls", "recording_device.cpp")
+HIP_INC = "/opt/rocm/include"
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(HIP_INC),
+                                reason="needs g++ and the HIP headers")
+
+KINDS = {1: "upload", 2: "articulate", 3: "window", 4: "primary", 5: "trace", 6: "fans", 7: "adjoint", 8: "reduce"}
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("host_calls")
+    jobs, objs = [], []
+    for s in [os.path.join(CSRC, f) for f in ("capi.cpp", "scene.cpp", "nplate.cpp", "propagate.cpp", "spad.cpp")] + [DEVICE]:
+        o = tmp / (os.path.basename(s) + ".o")
+        objs.append(str(o))
+        jobs.append(subprocess.Popen(["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", HIP_INC,
+                                      "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", s, "-o", str(o)]))
+    assert [j.wait() for j in jobs] == [0] * len(jobs)
+    out = tmp / "libcalls.so"
+    # (its own HIP calls, not those of a runtime that the process has loaded)
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", *objs, "-o", str(out)], check=True)
+    return out
+
+
+class Device:
+    """One fresh copy of the library and its recording device."""
+
+    def __init__(self, path):
+        self.lib = lib = C.CDLL(str(path))
+        lib.srp_last_error.restype = C.c_char_p
+        lib.dev_used.restype = lib.dev_faults.restype = lib.dev_log.restype = C.c_int64
+        lib.dev_limit.argtypes = [C.c_int64]
+        lib.dev_log.argtypes = [C.c_void_p, C.c_int64]
+        V, I32, I64 = C.c_void_p, C.c_int32, C.c_int64
+        lib.srp_build_scene.argtypes = [V, I64, V, I64, V, V, V, I32, V, I32, C.POINTER(V)]
+        lib.srp_eval.argtypes = [V, V, V, V, V]
+        lib.srp_eval_batch.argtypes = lib.srp_eval_batch_noalloc.argtypes = [V, I64, V, V]
+        lib.srp_eval_grad_batch.argtypes = [V, I64, V, V, I64, V]
+        lib.srp_eval_grad.argtypes = [V] * 7
+        lib.srp_plan_create.argtypes = [V, I64, I32, V, V, I64, C.POINTER(V)]
+        lib.srp_plan_update.argtypes = [V, V, I64]
+        lib.srp_set_schedule.argtypes = [I32, I32]
+
+    def error(self):
+        return self.lib.srp_last_error().decode()
+
+    def scene(self, mesh):
+        verts, tris, tm, tn, mats, nodes = _mesh_arrays(mesh)
+        h = C.c_void_p()
+        rc = self.lib.srp_build_scene(L.ptr(verts), len(verts), L.ptr(tris), len(tris), L.ptr(tm), L.ptr(tn), mats,
+                                      len(mesh.mats), nodes, len(nodes), C.byref(h))
+        assert rc == 0, self.error()
+        return h
+
+    def items(self, entries):
+        """entries: (scene, params[, angles]) per item; angles are kept alive with the array."""
+        arr = (L.srp_batch_item * len(entries))()
+        arr.keep = []
+        for k, (sc, p, *ang) in enumerate(entries):
+            arr[k].scene, arr[k].angles, arr[k].p = sc, None, p
+            if ang:
+                a = np.ascontiguousarray(ang[0], np.float64)
+                arr.keep.append(a)
+                arr[k].angles = a.ctypes.data
+        return arr
+
+    def log(self):
+        n = self.lib.dev_log(None, 0)
+        a = np.zeros((n, 8), np.int64)
+        self.lib.dev_log(a.ctypes.data, n)
+        self.lib.dev_clear()
+        return [(KINDS[r[0]], *r[1:].tolist()) for r in a]
+
+    def batch(self, entries, grad=False, noalloc=False):
+        arr, n = self.items(entries), len(entries)
+        self.lib.dev_clear()
+        if grad:
+            return self.lib.srp_eval_grad_batch(arr, n, 1 << 20, 1 << 20, 1 << 20, None)
+        return (self.lib.srp_eval_batch_noalloc if noalloc else self.lib.srp_eval_batch)(arr, n, 1 << 20, None)
+
+
+@pytest.fixture
+def dev(so, tmp_path):
+    shutil.copy(so, tmp_path / "lib.so")   # (a library of another path is loaded, and starts, anew)
+    return Device(tmp_path / "lib.so")
+
+
+SUN = (0.3, -0.5, 0.8)
+
+
+def test_a_failed_result_allocation_does_not_launch_without_a_result(dev):
+    """A scene's first evaluation allocates its result; when that fails, the next
+    one must not launch with the half that succeeded."""
+    sc = dev.scene(synth.box_wing())
+    p, r = params(SUN, 64, 1), L.srp_result()
+    dev.lib.dev_fail_host(1)
+    assert dev.lib.srp_eval(sc, C.byref(p), C.byref(r), None, None) == L.SRP_ERR_OOM
+    assert dev.lib.srp_eval(sc, C.byref(p), C.byref(r), None, None) == 0, dev.error()
+    assert dev.lib.dev_faults() == 0 and dev.log()[-1][0] == "reduce"
