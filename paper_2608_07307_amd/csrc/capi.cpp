@@ -501,30 +501,29 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     // 4145 / 4652, 7551 / 8080.  A separate launch costs about 4 ns per patch and a microsecond per
     // pass; inline, a launch ends on a few patches of up to 1.7 ms each, which weighs
     // more where a launch is small and rays are expensive.
+    // (A unit list numbers its passes with 32 bits: a batch of more keeps its fans inline.)
     int64_t fan_patches = 0, fan_rays = INT64_MAX, fan_tris = INT64_MAX;
-    for (int64_t k = 0; k < n; ++k)
-        if (!grad && items[k].p.bounces > 0 && items[k].p.n_diffuse > 0) {
-            fan_patches += L.patch_base[k + 1] - L.patch_base[k];
-            fan_rays = std::min<int64_t>(fan_rays, (int64_t)items[k].p.bounces * items[k].p.n_diffuse);
-            fan_tris = std::min<int64_t>(fan_tris, items[k].scene->h.n_tris);
-        }
-    if (fan_patches > 0) {
-        const int64_t resident = (int64_t)g_ws.n_cu * fan_blocks_per_cu(L.count) * (BLOCK / 64);
-        const bool dear = roomy && fan_rays >= 16 && (fan_tris >= 32768 || fan_patches < 8 * resident);
-        L.fans_inline = fan_patches >= 2 * resident && !dear;
-    }
     // partial slots: one per pass of 64 tasks (emitter, slice of FAN_SLICE fan rays), at
     // most bounces x ceil(n_diffuse / FAN_SLICE) per patch
     L.fan_base.assign(n + 1, 0);
     for (int64_t k = 0; k < n; ++k) {
         L.fan_base[k] = L.total_fan_slots;
         const srp_eval_params &p = items[k].p;
-        if (!grad && p.bounces > 0 && p.n_diffuse > 0) {
-            const int64_t np = L.patch_base[k + 1] - L.patch_base[k];
-            L.total_fan_slots += np * p.bounces * ((p.n_diffuse + FAN_SLICE - 1) / FAN_SLICE);
-        }
+        if (grad || p.bounces == 0 || p.n_diffuse == 0) continue;
+        const int64_t np = L.patch_base[k + 1] - L.patch_base[k];
+        L.total_fan_slots += np * p.bounces * ((p.n_diffuse + FAN_SLICE - 1) / FAN_SLICE);
+        fan_patches += np;
+        fan_rays = std::min<int64_t>(fan_rays, (int64_t)p.bounces * p.n_diffuse);
+        fan_tris = std::min<int64_t>(fan_tris, items[k].scene->h.n_tris);
     }
     L.fan_base[n] = L.total_fan_slots;
+    constexpr int64_t MAX_UNITS = (int64_t)1 << 31;
+    if (fan_patches > 0) {
+        const int64_t resident = (int64_t)g_ws.n_cu * fan_blocks_per_cu(L.count) * (BLOCK / 64);
+        const bool dear = roomy && L.total_fan_slots <= MAX_UNITS && fan_rays >= 16 &&
+                          (fan_tris >= 32768 || fan_patches < 8 * resident);
+        L.fans_inline = fan_patches >= 2 * resident && !dear;
+    }
     // the fan launch's unit list: room for every pass slot (each patch lists at
     // most its slots)
     L.total_units = L.fans_inline ? 0 : L.total_fan_slots;
@@ -532,7 +531,7 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     // at most a fourth of what is left)
     if (L.total_chunks > ((int64_t)1 << 31))
         return fail(SRP_ERR_ARG, "batch too large: more than 2^31 chunks (split it or raise patches per chunk)");
-    if (L.total_units > ((int64_t)1 << 31))
+    if (L.total_units > MAX_UNITS)
         return fail(SRP_ERR_ARG, "batch too large: more than 2^31 diffuse work units (split it)");
 
     // articulation slots: the scene's current slot, or one per distinct angle

@@ -116,3 +116,29 @@ def test_a_failed_result_allocation_does_not_launch_without_a_result(dev):
     assert dev.lib.srp_eval(sc, C.byref(p), C.byref(r), None, None) == L.SRP_ERR_OOM
     assert dev.lib.srp_eval(sc, C.byref(p), C.byref(r), None, None) == 0, dev.error()
     assert dev.lib.dev_faults() == 0 and dev.log()[-1][0] == "reduce"
+
+
+def _grid_mesh(n_tris):
+    """A plate of at least n_tris triangles."""
+    k = int(np.ceil(np.sqrt(n_tris / 2)))
+    return synth.plate((-1, -1, 0), (2, 0, 0), (0, 2, 0), nu=k, nv=k)
+
+
+def test_large_diffuse_batches_of_expensive_scenes_are_taken(dev):
+    """130 evaluations at 8192^2 with 16 diffuse rays hold 2.2e9 fan passes, more
+    than a unit list can number: they run as sub-batches, as any batch beyond
+    the workspace cap, and the choice between fans in the trace kernel and a
+    list must not refuse them.  A captured plan of that many is not split, and
+    traces its fans without a list."""
+    sc = dev.scene(_grid_mesh(40000))
+    entries = [(sc, params(SUN, 8192, 2, diffuse=16))] * 130
+    assert 130 * 1024 * 1024 * 2 * 8 > 2 ** 31
+    assert dev.batch(entries) == 0, dev.error()
+    log = dev.log()
+    assert sum(r[1] for r in log if r[0] == "reduce") == 130
+    assert all(r[4] for r in log if r[0] == "trace")       # (sub-batches keep their lists)
+    h = C.c_void_p()
+    arr = dev.items(entries)
+    assert dev.lib.srp_plan_create(arr, 130, 0, 1 << 20, None, 0, C.byref(h)) == 0, dev.error()
+    trace = [r for r in dev.log() if r[0] == "trace"]
+    assert len(trace) == 1 and trace[0][3] == 1 and trace[0][4] == 0
