@@ -476,6 +476,10 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     L.sch = (force.ppc && force.bpc) ? force : pick_schedule(items, n, grad, L.total_patches, occ);
     if (force.ppc) L.sch.ppc = force.ppc;
     if (force.bpc) L.sch.bpc = std::min(force.bpc, occ);
+    constexpr int64_t MAX_CHUNKS = (int64_t)1 << 31;
+    // (a gradient batch is not refused for its chunks: their size is no part of its results)
+    while (grad && L.sch.ppc < MAX_PPC && L.total_patches / L.sch.ppc + n > MAX_CHUNKS)
+        L.sch.ppc = std::min(2 * L.sch.ppc, MAX_PPC);
     L.group.assign(n, 0);
     L.n_groups.assign(n, 0);
     for (int64_t k = 0; k < n; ++k) {
@@ -529,7 +533,7 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     L.total_units = L.fans_inline ? 0 : L.total_fan_slots;
     // the work counters are 32-bit and overshoot their range by less than it (a wave takes
     // at most a fourth of what is left)
-    if (L.total_chunks > ((int64_t)1 << 31))
+    if (L.total_chunks > MAX_CHUNKS)
         return fail(SRP_ERR_ARG, "batch too large: more than 2^31 chunks (split it or raise patches per chunk)");
     if (L.total_units > MAX_UNITS)
         return fail(SRP_ERR_ARG, "batch too large: more than 2^31 diffuse work units (split it)");

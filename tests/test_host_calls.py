@@ -142,3 +142,14 @@ def test_large_diffuse_batches_of_expensive_scenes_are_taken(dev):
     assert dev.lib.srp_plan_create(arr, 130, 0, 1 << 20, None, 0, C.byref(h)) == 0, dev.error()
     trace = [r for r in dev.log() if r[0] == "trace"]
     assert len(trace) == 1 and trace[0][3] == 1 and trace[0][4] == 0
+
+
+@pytest.mark.parametrize("schedule", [(0, 0), (1, 4), (5, 2)])
+def test_large_gradient_batches_are_taken_at_any_schedule(dev, schedule):
+    """8,200 evaluations at 8192^2 hold 8.6e9 patches.  A gradient batch's trace is
+    handed out in the schedule's chunks, whose counters are 32-bit; its size
+    alone, and patches per chunk set for forward batches, must not refuse it."""
+    sc = dev.scene(synth.box_wing())
+    dev.lib.srp_set_schedule(*schedule)
+    assert dev.batch([(sc, params(SUN, 8192, 0))] * 8200, grad=True) == 0, dev.error()
+    assert sum(r[1] for r in dev.log() if r[0] == "reduce") == 8200
