@@ -317,9 +317,12 @@ struct Layout {
     std::vector<int64_t> slice_base;   // first range sum of every item, then the total
     std::vector<size_t> emit_off;   // emitter records of each item with diffuse fans (0: none)
     std::vector<int> grad_n;   // gradient partial doubles per chunk of each item (allocation and kernel)
-    int64_t max_groups = 0;
     std::vector<int> group;      // adjoint: patches per gradient group of each item
     std::vector<int64_t> n_groups;
+    int adj_waves = 1;           // waves per block of the adjoint kernel
+    std::vector<uint32_t> adj_base;    // its blocks before each item, then the total
+    uint32_t adj_most = 0;       // most blocks of any item
+    size_t o_abase = 0;
     std::vector<size_t> chain_off;
     int grid = 1, fan_grid = 0, wb = 1;
     // primary hits by rasterisation (k_primary): the items it serves, their first
@@ -329,8 +332,10 @@ struct Layout {
     std::vector<int64_t> vis_base;
     std::vector<size_t> prim_off;
     int64_t vis_patches = 0;
-    int vis_tile = 0, vis_tiles = 0;
-    size_t o_vis = 0, o_vmask = 0;
+    int vis_tile = 0;
+    std::vector<uint32_t> tile_base;   // tiles before each item (those not rasterised have none), then the total
+    uint32_t tile_most = 0;            // most tiles of any item
+    size_t o_vis = 0, o_vmask = 0, o_tbase = 0;
     bool fans_inline = false;   // the trace kernel traces the fans itself (no fan launch)
     // captured forward plans of one patch per chunk: the patch order of the next
     // launch and the per-patch costs it is made from (layout_add_order)
@@ -489,9 +494,20 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         if (!grad) continue;
         L.group[k] = grad_group(np, grad_slots(items[k].scene, items[k].p.flags));
         L.n_groups[k] = (np + L.group[k] - 1) / L.group[k];
-        L.max_groups = std::max(L.max_groups, L.n_groups[k]);
+        L.adj_waves = std::max(L.adj_waves, L.group[k] / GROUP_PART);
     }
     L.chunk_base[n] = L.total_chunks;
+    if (grad) {
+        L.adj_base.assign(n + 1, 0);
+        int64_t at = 0;
+        for (int64_t k = 0; k < n; ++k) {
+            const int64_t nb = adjoint_blocks(L.n_groups[k], L.group[k], L.adj_waves);
+            L.adj_most = std::max(L.adj_most, (uint32_t)nb);
+            at += nb;
+            if (at > UINT32_MAX) at = UINT32_MAX;   // (a batch beyond any workspace)
+            L.adj_base[k + 1] = (uint32_t)at;
+        }
+    }
     // diffuse fans (forward only; emitters are chain hits of generation < bounces).
     // Either the trace kernel traces each patch's fans right after its chains, or it
     // lists every patch's non-empty fan passes and a fan kernel follows with one unit
@@ -576,15 +592,52 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         L.item_slot[k] = found;
     }
 
+    // the items whose primary hits are rasterised, and their tiles
+    L.item_vis.assign(n, 0);
+    L.vis_base.assign(n, 0);
+    L.prim_off.assign(n, 0);
+    L.roomy = roomy;
+    if (roomy && !L.count) {   // (a counting launch counts the traversal's tests)
+        double ratio = 0.6;
+        for (int64_t least : {RASTER_BIG_PATCHES, RASTER_MIN_PATCHES}) {
+            L.vis_patches = 0;
+            for (int64_t k = 0; k < n; ++k)
+                if (use_raster(items[k], ratio)) L.vis_patches += L.patch_base[k + 1] - L.patch_base[k];
+            if (L.vis_patches >= least) break;
+            L.vis_patches = 0;
+            if (least == RASTER_BIG_PATCHES) ratio = 0.25;
+        }
+        int64_t at = 0;
+        for (int64_t k = 0; k < n && L.vis_patches > 0; ++k) {
+            if (!use_raster(items[k], ratio)) continue;
+            L.item_vis[k] = 1;
+            L.vis_base[k] = at;
+            at += L.patch_base[k + 1] - L.patch_base[k];
+        }
+    }
+    if (L.vis_patches > 0) {
+        L.vis_tile = raster_tile(L.vis_patches);
+        const int pw = L.vis_tile / PATCH;
+        L.tile_base.assign(n + 1, 0);
+        for (int64_t k = 0; k < n; ++k) {
+            const uint32_t nt = L.item_vis[k] ? (uint32_t)((2 * L.tiles_x[k] + pw - 1) / pw) : 0;
+            L.tile_most = std::max(L.tile_most, nt * nt);
+            L.tile_base[k + 1] = L.tile_base[k] + nt * nt;
+        }
+    }
+
     // staging (uploaded every launch): descs | chunk_base | win |
-    // evaluation of every range sum | articulation jobs | their cosines and sines
+    // evaluation of every range sum | articulation jobs | their cosines and sines |
+    // the rasteriser's tiles and the adjoint's blocks before every item
     L.o_desc = 0;
     L.o_cbase = align_up(sizeof(EvalDesc) * n);
     L.o_win = align_up(L.o_cbase + sizeof(int64_t) * (n + 1));
     L.o_seval = align_up(L.o_win + sizeof(uint64_t) * WIN_STRIDE * n);
     L.o_jobs = align_up(L.o_seval + sizeof(uint32_t) * L.slice_base[n]);
     L.o_cs = align_up(L.o_jobs + sizeof(ArtJob) * L.slots.size());
-    L.stage_bytes = align_up(L.o_cs + sizeof(double) * L.total_cs);
+    L.o_tbase = align_up(L.o_cs + sizeof(double) * L.total_cs);
+    L.o_abase = align_up(L.o_tbase + sizeof(uint32_t) * L.tile_base.size());
+    L.stage_bytes = align_up(L.o_abase + sizeof(uint32_t) * L.adj_base.size());
     // device-only: articulation slots | patch partials | counts | emitter masks
     L.o_slots = L.stage_bytes;
     size_t off = L.o_slots;
@@ -630,37 +683,7 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         L.gslice_off[k] = goff;
         goff = align_up(goff + sizeof(double) * L.grad_n[k] * L.n_slices[k]);
     }
-    // primary hits
-    L.item_vis.assign(n, 0);
-    L.vis_base.assign(n, 0);
-    L.prim_off.assign(n, 0);
-    L.roomy = roomy;
-    if (roomy && !L.count) {   // (a counting launch counts the traversal's tests)
-        double ratio = 0.6;
-        for (int64_t least : {RASTER_BIG_PATCHES, RASTER_MIN_PATCHES}) {
-            L.vis_patches = 0;
-            for (int64_t k = 0; k < n; ++k)
-                if (use_raster(items[k], ratio)) L.vis_patches += L.patch_base[k + 1] - L.patch_base[k];
-            if (L.vis_patches >= least) break;
-            L.vis_patches = 0;
-            if (least == RASTER_BIG_PATCHES) ratio = 0.25;
-        }
-        int64_t at = 0;
-        for (int64_t k = 0; k < n && L.vis_patches > 0; ++k) {
-            if (!use_raster(items[k], ratio)) continue;
-            L.item_vis[k] = 1;
-            L.vis_base[k] = at;
-            at += L.patch_base[k + 1] - L.patch_base[k];
-        }
-    }
     if (L.vis_patches > 0) {
-        L.vis_tile = raster_tile(L.vis_patches);
-        const int pw = L.vis_tile / PATCH;
-        for (int64_t k = 0; k < n; ++k)
-            if (L.item_vis[k]) {
-                const int nt = (2 * L.tiles_x[k] + pw - 1) / pw;
-                L.vis_tiles = std::max(L.vis_tiles, nt * nt);
-            }
         L.o_vmask = align_up(goff);
         L.o_vis = align_up(L.o_vmask + sizeof(uint64_t) * L.vis_patches);
         goff = align_up(L.o_vis + sizeof(uint2) * 64 * L.vis_patches);
@@ -714,6 +737,8 @@ void staging_fill(const Layout &L, const srp_batch_item *items, const BatchOut &
     uint32_t *seval = reinterpret_cast<uint32_t *>(H + L.o_seval);
     for (int64_t k = 0; k < n; ++k)
         for (int64_t q = L.slice_base[k]; q < L.slice_base[k + 1]; ++q) seval[q] = (uint32_t)k;
+    std::copy(L.tile_base.begin(), L.tile_base.end(), reinterpret_cast<uint32_t *>(H + L.o_tbase));
+    std::copy(L.adj_base.begin(), L.adj_base.end(), reinterpret_cast<uint32_t *>(H + L.o_abase));
     ArtJob *jobs = reinterpret_cast<ArtJob *>(H + L.o_jobs);
     double *cs = reinterpret_cast<double *>(H + L.o_cs);
     std::vector<int> slot_clamped(L.slots.size(), 0);
@@ -856,7 +881,8 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
         HIPCHK(hipEventRecord(ev.first, stream));
     }
     if (L.vis_patches > 0) {
-        e = launch_primary(d_desc, (int)L.n, d_win, L.vis_tile, L.vis_tiles, stream);
+        e = launch_primary(d_desc, (int)L.n, d_win, L.vis_tile, reinterpret_cast<const uint32_t *>(Dv + L.o_tbase),
+                           L.tile_base[L.n], L.tile_most, stream);
         if (e) return fail(SRP_ERR_DEVICE, std::string("primary kernel: ") + hipGetErrorString((hipError_t)e));
     }
     PatchOut *d_fan_out = nullptr;
@@ -875,7 +901,8 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
         if (e) return fail(SRP_ERR_DEVICE, std::string("fan kernel: ") + hipGetErrorString((hipError_t)e));
     }
     if (L.grad) {
-        e = launch_adjoint(d_desc, (int)L.n, L.max_groups, *std::max_element(L.group.begin(), L.group.end()), d_patches, L.dir, L.max_grad_n, stream);
+        e = launch_adjoint(d_desc, (int)L.n, reinterpret_cast<const uint32_t *>(Dv + L.o_abase), L.adj_base[L.n],
+                           L.adj_most, L.adj_waves, d_patches, L.dir, L.max_grad_n, stream);
         if (e) return fail(SRP_ERR_DEVICE, std::string("adjoint kernel: ") + hipGetErrorString((hipError_t)e));
     }
     if (profile) {   // the ray kernels: primary hits, trace, then fans or the adjoint
@@ -1074,7 +1101,8 @@ int plan_refill(PlanImpl *P, const srp_batch_item *items, int64_t n, bool *compa
         L2.o_emask != L.o_emask || L2.o_fanout != L.o_fanout || L2.o_fancnt != L.o_fancnt ||
         L2.o_queue != L.o_queue || L2.o_spill != L.o_spill || L2.slots.size() != L.slots.size() ||
         L2.o_jobs != L.o_jobs || L2.o_cs != L.o_cs || L2.o_slots != L.o_slots || L2.ordered != L.ordered ||
-        L2.item_vis != L.item_vis || L2.vis_tile != L.vis_tile || L2.o_vis != L.o_vis || L2.o_vmask != L.o_vmask ||
+        L2.item_vis != L.item_vis || L2.vis_tile != L.vis_tile || L2.tile_base != L.tile_base ||
+        L2.adj_base != L.adj_base || L2.adj_waves != L.adj_waves || L2.o_vis != L.o_vis || L2.o_vmask != L.o_vmask ||
         L2.o_order != L.o_order || L2.o_cost != L.o_cost)
         return SRP_OK;
     for (size_t q = 0; q < L.slots.size(); ++q)
@@ -1373,7 +1401,7 @@ int srp_eval_batch_noalloc(const srp_batch_item *items, int64_t n_items, srp_res
     Layout L;
     if ((rc = layout_build(items, n_items, false, Schedule(), &L))) return rc;
     // (buffers that only buy speed only where they fit beside the whole grid's stacks)
-    if (L.dev_bytes > NOALLOC_SCRATCH_BYTES &&
+    if ((L.dev_bytes > NOALLOC_SCRATCH_BYTES || L.stage_bytes > NOALLOC_STAGE_BYTES) &&
         (rc = layout_build(items, n_items, false, Schedule(), &L, false)))
         return rc;
     if ((rc = layout_fit(&L, NOALLOC_SCRATCH_BYTES))) return rc;

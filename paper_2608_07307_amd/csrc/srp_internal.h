@@ -344,9 +344,11 @@ int launch_window(const EvalDesc *d_desc, int n_evals, int blocks_x, uint64_t *d
 // window kernel reads them, so it runs first on the same stream.
 int launch_articulate(const ArtJob *d_jobs, int n_jobs, void *stream);
 // Primary hits of the evaluations whose descriptor has vis, on tiles of tile x
-// tile pixels (16 or 8); max_tiles: the most tiles of any of them.  Runs
+// tile pixels (16 or 8).  d_tile_base: the tiles before each evaluation (none of
+// one without vis), n_tiles in all, max_tiles of one evaluation at most.  Runs
 // after the window kernel and before the trace kernel (primary.hip).
-int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, int tile, int max_tiles, void *stream);
+int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, int tile, const uint32_t *d_tile_base,
+                   uint32_t n_tiles, uint32_t max_tiles, void *stream);
 // d_spill: grid_blocks * BLOCK * STACK_SPILL words; chunk counts below 2^31.
 // d_fan_out, d_fan_counts (forward, diffuse rays on): the fan pass partial
 // slots.  With fans_inline the trace kernel also traces every patch's diffuse
@@ -365,11 +367,35 @@ int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_eval
                  uint64_t *d_fan_counts, bool fans_inline, int4 *d_fan_units, int blocks_per_cu,
                  const uint32_t *d_order, uint32_t *d_cost, void *stream);
 // Gradient partials of every group from the chains and hit counts that the
-// trace kernel wrote (max_groups: the most groups of any evaluation; max_group:
-// the largest group;
-// lds_grad_doubles: the largest grad_n).
-int launch_adjoint(const EvalDesc *d_desc, int n_evals, int64_t max_groups, int max_group, const PatchOut *d_patches,
-                   bool dir, int lds_grad_doubles, void *stream);
+// trace kernel wrote, in blocks of block_waves = max group / GROUP_PART waves.
+// d_block_base: the blocks before each evaluation (adjoint_blocks of each),
+// n_blocks in all, max_blocks of one evaluation at most.  lds_grad_doubles: the
+// largest grad_n.
+int launch_adjoint(const EvalDesc *d_desc, int n_evals, const uint32_t *d_block_base, uint32_t n_blocks,
+                   uint32_t max_blocks, int block_waves, const PatchOut *d_patches, bool dir, int lds_grad_doubles,
+                   void *stream);
+SRP_HD inline int64_t adjoint_blocks(int64_t n_groups, int group, int block_waves) {
+    return (n_groups * (group / GROUP_PART) + block_waves - 1) / block_waves;
+}
+// Blocks of such a launch per kernel launch at most (a dispatch counts its
+// work-items with 32 bits).
+constexpr uint32_t MAX_LAUNCH_BLOCKS = (uint32_t)1 << 22;
+
+// The evaluation that owns block b of a launch numbered through its batch: base[k]
+// blocks before evaluation k, base[n] > b in all, at most `most` of one.  Evaluations
+// of one size need no search: none before b / most can own b.
+template <class P>
+SRP_HD inline int block_owner(P base, int n, uint32_t b, uint32_t most) {
+    const uint32_t first = b / most;
+    int lo = (int)(first < (uint32_t)(n - 1) ? first : (uint32_t)(n - 1));
+    if (b < base[lo + 1]) return lo;
+    int hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (base[mid] <= b) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
 // Diffuse fans of the recorded emitters: one work unit per non-empty fan pass,
 // as the trace kernel listed them in d_fan_units (at most max_units); uses the
 // second set of queue counters and the same spill area as the trace kernel.

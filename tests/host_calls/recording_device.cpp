@@ -155,11 +155,27 @@ int launch_articulate(const ArtJob *, int n_jobs, void *) {
     note(ARTICULATE, n_jobs);
     return 0;
 }
+// Every block of a launch numbered through the batch finds its evaluation.
+void check_owners(const uint32_t *base, int n, uint32_t total, uint32_t most) {
+    if (base[0] != 0 || base[n] != total) ++g_faults;
+    for (int k = 0; k < n; ++k)
+        if (base[k + 1] - base[k] > most) ++g_faults;
+    for (uint32_t b = 0; b < total; ++b) {
+        const int e = block_owner(base, n, b, most);
+        if (e < 0 || e >= n || b < base[e] || b >= base[e + 1]) ++g_faults;
+    }
+}
 // PRIMARY: evaluations, of them rasterised, tile, blocks launched
-int launch_primary(const EvalDesc *d, int n_evals, const uint64_t *, int tile, int max_tiles, void *) {
+int launch_primary(const EvalDesc *d, int n_evals, const uint64_t *, int tile, const uint32_t *tile_base,
+                   uint32_t n_tiles, uint32_t max_tiles, void *) {
     int64_t with = 0;
-    for (int k = 0; k < n_evals; ++k) with += d[k].vis != nullptr;
-    note(PRIMARY, n_evals, with, tile, (int64_t)max_tiles * n_evals);
+    for (int k = 0; k < n_evals; ++k) {
+        with += d[k].vis != nullptr;
+        const uint32_t nt = d[k].vis ? (uint32_t)((16 * d[k].tiles_x + tile - 1) / tile) : 0;   // (the whole patches' tiles)
+        if (tile_base[k + 1] - tile_base[k] != nt * nt) ++g_faults;
+    }
+    check_owners(tile_base, n_evals, n_tiles, max_tiles);
+    note(PRIMARY, n_evals, with, tile, n_tiles);
     return 0;
 }
 // TRACE: evaluations, chunks, fans traced inside, fan units listed
@@ -169,9 +185,16 @@ int launch_trace(const EvalDesc *, const int64_t *, int n_evals, const uint64_t 
     note(TRACE, n_evals, total_chunks, d_fan_out && fans_inline, d_fan_units != nullptr);
     return 0;
 }
-// ADJOINT: evaluations, blocks launched
-int launch_adjoint(const EvalDesc *, int n_evals, int64_t max_groups, int, const PatchOut *, bool, int, void *) {
-    note(ADJOINT, n_evals, max_groups * n_evals);
+// ADJOINT: evaluations, blocks launched, waves per block; every group in a block of its own evaluation
+int launch_adjoint(const EvalDesc *d, int n_evals, const uint32_t *block_base, uint32_t n_blocks, uint32_t max_blocks,
+                   int block_waves, const PatchOut *, bool, int, void *) {
+    for (int k = 0; k < n_evals; ++k) {
+        const int64_t nb = block_base[k + 1] - block_base[k], parts = d[k].group / GROUP_PART;
+        if (nb * block_waves < d[k].n_groups * parts || (nb - 1) * block_waves >= d[k].n_groups * parts) ++g_faults;
+        if (parts < 1 || parts > block_waves || d[k].n_groups * d[k].group < d[k].n_patches) ++g_faults;
+    }
+    check_owners(block_base, n_evals, n_blocks, max_blocks);
+    note(ADJOINT, n_evals, n_blocks, block_waves);
     return 0;
 }
 int launch_fans(const EvalDesc *, const uint64_t *, int64_t max_units, uint32_t *, uint32_t *, PatchOut *, uint64_t *,

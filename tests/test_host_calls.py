@@ -153,3 +153,28 @@ def test_large_gradient_batches_are_taken_at_any_schedule(dev, schedule):
     dev.lib.srp_set_schedule(*schedule)
     assert dev.batch([(sc, params(SUN, 8192, 0))] * 8200, grad=True) == 0, dev.error()
     assert sum(r[1] for r in dev.log() if r[0] == "reduce") == 8200
+
+
+def _tiles(n, px):
+    return (-(-(16 * -(-n // 16)) // px)) ** 2
+
+
+@pytest.mark.parametrize("small", [0, 1, 500, 3000])
+def test_launches_are_numbered_through_uneven_batches(dev, small):
+    """One fine image beside many coarse ones: the rasteriser's and the adjoint's
+    blocks are those of the images themselves, not the largest one's for every
+    evaluation, and every block finds its own evaluation."""
+    fine, coarse = dev.scene(_grid_mesh(2000)), dev.scene(synth.box_wing())
+    entries = [(coarse, params(SUN, 64, 1))] * small
+    entries.insert(small // 3, (fine, params(SUN, 2048, 1)))
+    if small > 1:   # another rasterised size behind the others
+        entries.append((fine, params(SUN, 300, 1)))
+    assert dev.batch(entries, grad=True) == 0, dev.error()
+    log = dev.log()
+    primary = [r for r in log if r[0] == "primary"]
+    adjoint = [r for r in log if r[0] == "adjoint"]
+    px = primary[0][3]
+    with_vis = [e for e in entries if e[0] is fine]
+    assert primary[0][2] == len(with_vis) and primary[0][4] == sum(_tiles(p.n, px) for _, p in with_vis)
+    patches = [4 * (-(-p.n // 16)) ** 2 for _, p in entries]
+    assert adjoint[0][2] <= sum(-(-k // 8) for k in patches) and dev.lib.dev_faults() == 0
