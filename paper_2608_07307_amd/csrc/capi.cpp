@@ -295,6 +295,33 @@ struct SlotRec {
     size_t off;      // device offset of the slot
 };
 
+// What a layout may spend on device memory that results do not depend on.
+// Adjoint chains take 256 (B + 1) bytes per patch, four to twenty times all else an
+// adjoint batch needs, so a launch without room for them traces and sweeps its
+// patches a window after the other.
+enum Room {
+    ROOM_LEAST,   // chains of CHAINS_LEAST bytes at a time
+    ROOM_LEAN,    // of CHAINS_LEAN (a batch of fewer has them whole); nothing that only buys speed
+    ROOM_FULL,    // rasterised hits, unit lists of big fan launches, whole chains
+};
+constexpr size_t CHAINS_LEAST = (size_t)4 << 20, CHAINS_LEAN = (size_t)1 << 30;
+
+// Patches [p0, p1) (whole gradient groups) of an evaluation, and the device
+// offset of their chains.
+struct ChainPiece {
+    int64_t item, p0, p1;
+    size_t off;
+    bool operator==(const ChainPiece &o) const {
+        return item == o.item && p0 == o.p0 && p1 == o.p1 && off == o.off;
+    }
+};
+// Pieces [first, first + count) whose chains are held at the same time.
+struct ChainWindow {
+    int64_t first, count;
+    int64_t chunks;            // of the trace kernel
+    uint32_t blocks, most;     // of the adjoint kernel; of one piece at most
+};
+
 // Everything about a batch that does not change when only Sun directions,
 // pressures, references or hinge-angle values change.
 struct Layout {
@@ -324,10 +351,13 @@ struct Layout {
     uint32_t adj_most = 0;       // most blocks of any item
     size_t o_abase = 0;
     std::vector<size_t> chain_off;
+    std::vector<ChainPiece> pieces;     // empty: whole chains
+    std::vector<ChainWindow> windows;
+    size_t o_pdesc = 0, o_pwin = 0, o_pcbase = 0, o_pabase = 0;   // the pieces' descriptors, window slots, chunk and block bases
     int grid = 1, fan_grid = 0, wb = 1;
     // primary hits by rasterisation (k_primary): the items it serves, their first
     // patch in its buffers, its tile and the most tiles of any item
-    bool roomy = true;   // buffers that only buy speed are allowed: rasterised hits, unit lists of big fan launches
+    Room room = ROOM_FULL;
     std::vector<char> item_vis;
     std::vector<int64_t> vis_base;
     std::vector<size_t> prim_off;
@@ -442,9 +472,11 @@ constexpr int64_t RASTER_MIN_PATCHES = 16384, RASTER_BIG_PATCHES = 131072;
 int raster_tile(int64_t patches) { return patches >= RASTER_BIG_PATCHES ? 16 : 8; }
 
 int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule force, Layout *Lp,
-                 bool roomy = true) {
+                 Room room = ROOM_FULL) {
     Layout &L = *Lp;
     L = Layout();
+    L.room = room;
+    const bool roomy = room == ROOM_FULL;
     L.n = n;
     L.grad = grad;
     L.chunk_base.assign(n + 1, 0);
@@ -596,7 +628,6 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     L.item_vis.assign(n, 0);
     L.vis_base.assign(n, 0);
     L.prim_off.assign(n, 0);
-    L.roomy = roomy;
     if (roomy && !L.count) {   // (a counting launch counts the traversal's tests)
         double ratio = 0.6;
         for (int64_t least : {RASTER_BIG_PATCHES, RASTER_MIN_PATCHES}) {
@@ -626,9 +657,40 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         }
     }
 
+    // windows of the adjoint's chains
+    size_t chain_bytes = 0, window_bytes = 0;
+    const size_t chain_room = room == ROOM_LEAST ? CHAINS_LEAST : CHAINS_LEAN;
+    auto patch_chain = [&](int64_t k) { return sizeof(uint32_t) * 64 * (size_t)(items[k].p.bounces + 1); };
+    for (int64_t k = 0; k < n && grad; ++k) chain_bytes += patch_chain(k) * (L.patch_base[k + 1] - L.patch_base[k]);
+    if (!roomy && chain_bytes > chain_room) {
+        size_t at = chain_room;   // (full: the first piece opens a window)
+        for (int64_t k = 0; k < n; ++k) {
+            const int64_t np = L.patch_base[k + 1] - L.patch_base[k];
+            const size_t group_bytes = patch_chain(k) * L.group[k];
+            for (int64_t p0 = 0, p1; p0 < np; p0 = p1) {
+                if (at + group_bytes > chain_room) {
+                    L.windows.push_back({(int64_t)L.pieces.size(), 0, 0, 0, 0});
+                    at = 0;
+                }
+                const int64_t fit = (int64_t)((chain_room - at) / group_bytes);   // groups
+                p1 = std::min(np, p0 + fit * L.group[k]);
+                L.pieces.push_back({k, p0, p1, at});
+                at = align_up(at + patch_chain(k) * (p1 - p0));
+                window_bytes = std::max(window_bytes, at);
+                ChainWindow &w = L.windows.back();
+                const int64_t nb = adjoint_blocks((p1 - p0 + L.group[k] - 1) / L.group[k], L.group[k], L.adj_waves);
+                ++w.count;
+                w.chunks += (p1 - p0 + L.sch.ppc - 1) / L.sch.ppc;
+                w.blocks += (uint32_t)nb;
+                w.most = std::max(w.most, (uint32_t)nb);
+            }
+        }
+    }
+
     // staging (uploaded every launch): descs | chunk_base | win |
     // evaluation of every range sum | articulation jobs | their cosines and sines |
-    // the rasteriser's tiles and the adjoint's blocks before every item
+    // the rasteriser's tiles and the adjoint's blocks before every item |
+    // the chain pieces' descs, win, chunks and blocks (a total after each window's)
     L.o_desc = 0;
     L.o_cbase = align_up(sizeof(EvalDesc) * n);
     L.o_win = align_up(L.o_cbase + sizeof(int64_t) * (n + 1));
@@ -637,7 +699,11 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     L.o_cs = align_up(L.o_jobs + sizeof(ArtJob) * L.slots.size());
     L.o_tbase = align_up(L.o_cs + sizeof(double) * L.total_cs);
     L.o_abase = align_up(L.o_tbase + sizeof(uint32_t) * L.tile_base.size());
-    L.stage_bytes = align_up(L.o_abase + sizeof(uint32_t) * L.adj_base.size());
+    L.o_pdesc = align_up(L.o_abase + sizeof(uint32_t) * L.adj_base.size());
+    L.o_pwin = align_up(L.o_pdesc + sizeof(EvalDesc) * L.pieces.size());
+    L.o_pcbase = align_up(L.o_pwin + sizeof(uint64_t) * WIN_STRIDE * L.pieces.size());
+    L.o_pabase = align_up(L.o_pcbase + sizeof(int64_t) * (L.pieces.size() + L.windows.size()));
+    L.stage_bytes = align_up(L.o_pabase + sizeof(uint32_t) * (L.pieces.size() + L.windows.size()));
     // device-only: articulation slots | patch partials | counts | emitter masks
     L.o_slots = L.stage_bytes;
     size_t off = L.o_slots;
@@ -670,13 +736,14 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     L.gslice_off.assign(n, 0);
     L.pslice_off.assign(n, 0);
     size_t goff = L.o_gpart;
+    for (ChainPiece &pc : L.pieces) pc.off += goff;
+    goff = align_up(goff + window_bytes);
     for (int64_t k = 0; k < n; ++k) {
         L.pslice_off[k] = goff;
         goff = align_up(goff + sizeof(SliceOut) * L.n_slices[k]);
         if (!grad) continue;
         L.chain_off[k] = goff;
-        goff = align_up(goff + sizeof(uint32_t) * 64 * (size_t)(items[k].p.bounces + 1) *
-                                   (L.patch_base[k + 1] - L.patch_base[k]));
+        if (L.pieces.empty()) goff = align_up(goff + patch_chain(k) * (L.patch_base[k + 1] - L.patch_base[k]));
         L.gpart_off[k] = goff;
         L.grad_n[k] = grad_slots(items[k].scene, items[k].p.flags);
         goff = align_up(goff + sizeof(double) * L.grad_n[k] * L.n_groups[k]);
@@ -811,7 +878,7 @@ void staging_fill(const Layout &L, const srp_batch_item *items, const BatchOut &
         D.ppc = L.sch.ppc;
         D.n_groups = L.n_groups[k];
         D.group = L.group[k];
-        D.chain = L.grad ? reinterpret_cast<uint32_t *>(Dv + L.chain_off[k]) : nullptr;
+        D.chain = L.grad && L.pieces.empty() ? reinterpret_cast<uint32_t *>(Dv + L.chain_off[k]) : nullptr;
         D.patch_base = L.patch_base[k];
         D.n_patches = L.patch_base[k + 1] - L.patch_base[k];
         const bool fans = L.fan_base[k + 1] > L.fan_base[k];
@@ -836,6 +903,37 @@ void staging_fill(const Layout &L, const srp_batch_item *items, const BatchOut &
         D.grad_out = (L.grad && bo.d_grad) ? bo.d_grad + k * bo.grad_stride : nullptr;
         D.hit_ids = (n == 1) ? bo.d_hit_ids : nullptr;
         D.hit_t = (n == 1) ? bo.d_hit_t : nullptr;
+    }
+    // the chain pieces: their evaluations' descriptors, cut to the piece (patches, groups
+    // and chains keep their numbers within the evaluation, so the chains' pointer
+    // lies the patches before it below the window)
+    EvalDesc *pdesc = reinterpret_cast<EvalDesc *>(H + L.o_pdesc);
+    uint64_t *pwin = reinterpret_cast<uint64_t *>(H + L.o_pwin);
+    for (size_t i = 0; i < WIN_STRIDE * L.pieces.size(); ++i) pwin[i] = enc_f64(INFINITY);
+    for (size_t i = 0; i < L.pieces.size(); ++i) {
+        const ChainPiece &pc = L.pieces[i];
+        EvalDesc &D = pdesc[i];
+        D = desc[pc.item];
+        D.patch0 = (int32_t)pc.p0;
+        D.n_patches = pc.p1;
+        D.n_groups = (pc.p1 - pc.p0 + D.group - 1) / D.group;
+        D.grad_part += (size_t)(pc.p0 / D.group) * D.grad_n;
+        D.chain = reinterpret_cast<uint32_t *>(reinterpret_cast<uintptr_t>(Dv) + L.pieces[i].off -
+                                               sizeof(uint32_t) * 64 * (size_t)(D.bounces + 1) * pc.p0);
+    }
+    int64_t *pcbase = reinterpret_cast<int64_t *>(H + L.o_pcbase);
+    uint32_t *pabase = reinterpret_cast<uint32_t *>(H + L.o_pabase);
+    for (const ChainWindow &w : L.windows) {
+        int64_t chunks = 0;
+        uint32_t blocks = 0;
+        for (int64_t i = w.first; i <= w.first + w.count; ++i) {
+            *pcbase++ = chunks;
+            *pabase++ = blocks;
+            if (i == w.first + w.count) break;
+            const EvalDesc &D = pdesc[i];
+            chunks += (D.n_patches - D.patch0 + D.ppc - 1) / D.ppc;
+            blocks += (uint32_t)adjoint_blocks(D.n_groups, D.group, L.adj_waves);
+        }
     }
 }
 
@@ -892,18 +990,43 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
         d_fan_counts = L.count ? reinterpret_cast<uint64_t *>(Dv + L.o_fancnt) : nullptr;
     }
     int4 *d_units = L.total_units > 0 ? reinterpret_cast<int4 *>(Dv + L.o_units) : nullptr;
-    e = launch_trace(d_desc, d_cbase, (int)L.n, d_win, L.total_chunks, d_queue, d_spill, d_patches, d_counts, L.count,
-                     L.grid, d_fan_out, d_fan_counts, L.fans_inline, d_units, L.sch.bpc, d_order, d_cost, stream);
-    if (e) return fail(SRP_ERR_DEVICE, std::string("trace kernel: ") + hipGetErrorString((hipError_t)e));
+    const auto trace_failed = [](int e) {
+        return fail(SRP_ERR_DEVICE, std::string("trace kernel: ") + hipGetErrorString((hipError_t)e));
+    };
+    const auto adjoint_failed = [](int e) {
+        return fail(SRP_ERR_DEVICE, std::string("adjoint kernel: ") + hipGetErrorString((hipError_t)e));
+    };
+    if (L.windows.empty()) {
+        e = launch_trace(d_desc, d_cbase, (int)L.n, d_win, L.total_chunks, d_queue, d_spill, d_patches, d_counts,
+                         L.count, L.grid, d_fan_out, d_fan_counts, L.fans_inline, d_units, L.sch.bpc, d_order, d_cost,
+                         stream);
+        if (e) return trace_failed(e);
+    }
     if (L.total_units > 0) {
         e = launch_fans(d_desc, d_win, L.total_units, d_queue, d_spill, d_fan_out, d_fan_counts, d_units, L.count,
                         L.fan_grid, stream);
         if (e) return fail(SRP_ERR_DEVICE, std::string("fan kernel: ") + hipGetErrorString((hipError_t)e));
     }
-    if (L.grad) {
+    if (L.grad && L.windows.empty()) {
         e = launch_adjoint(d_desc, (int)L.n, reinterpret_cast<const uint32_t *>(Dv + L.o_abase), L.adj_base[L.n],
                            L.adj_most, L.adj_waves, d_patches, L.dir, L.max_grad_n, stream);
-        if (e) return fail(SRP_ERR_DEVICE, std::string("adjoint kernel: ") + hipGetErrorString((hipError_t)e));
+        if (e) return adjoint_failed(e);
+    }
+    // (a window's trace overwrites the chains that the sweep before it read)
+    for (size_t w = 0; w < L.windows.size(); ++w) {
+        const ChainWindow &W = L.windows[w];
+        const EvalDesc *d_pieces = reinterpret_cast<const EvalDesc *>(Dv + L.o_pdesc) + W.first;
+        uint64_t *d_pwin = reinterpret_cast<uint64_t *>(Dv + L.o_pwin) + WIN_STRIDE * W.first;
+        const int64_t at = W.first + (int64_t)w;   // (each window's bases end with their total)
+        e = launch_window(d_pieces, (int)W.count, L.wb, d_pwin, d_queue, stream);
+        if (e) return fail(SRP_ERR_DEVICE, std::string("window kernel: ") + hipGetErrorString((hipError_t)e));
+        e = launch_trace(d_pieces, reinterpret_cast<const int64_t *>(Dv + L.o_pcbase) + at, (int)W.count, d_pwin,
+                         W.chunks, d_queue, d_spill, d_patches, d_counts, L.count, L.grid, nullptr, nullptr, false,
+                         nullptr, L.sch.bpc, nullptr, nullptr, stream);
+        if (e) return trace_failed(e);
+        e = launch_adjoint(d_pieces, (int)W.count, reinterpret_cast<const uint32_t *>(Dv + L.o_pabase) + at, W.blocks,
+                           W.most, L.adj_waves, d_patches, L.dir, L.max_grad_n, stream);
+        if (e) return adjoint_failed(e);
     }
     if (profile) {   // the ray kernels: primary hits, trace, then fans or the adjoint
         HIPCHK(hipEventRecord(ev.second, stream));
@@ -948,8 +1071,9 @@ int run_batch(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
         HIPCHK(hipStreamWaitEvent(stream, g_ws.done, 0));
     }
     rc = ws_reserve(L.dev_bytes, L.stage_bytes);   // (waits for the last batch to grow)
-    if (rc == SRP_ERR_OOM) {   // no room: without the buffers that only buy speed
-        if ((rc = layout_build(items, n, grad, force, &L, false))) return rc;
+    for (Room room : {ROOM_LEAN, ROOM_LEAST}) {    // no room: with less
+        if (rc != SRP_ERR_OOM || (room == ROOM_LEAST && !grad)) break;
+        if ((rc = layout_build(items, n, grad, force, &L, room))) return rc;
         rc = ws_reserve(L.dev_bytes, L.stage_bytes);
     }
     if (rc) return rc;
@@ -1023,15 +1147,14 @@ int plan_make(const srp_batch_item *items, int64_t n, bool grad, const BatchOut 
     if (!P) return fail(SRP_ERR_OOM, "host allocation failed");
     P->bo = bo;
     // (buffers that only buy speed only while the plan's own stays within the workspace cap and fits)
-    for (bool roomy : {true, false}) {
-        if ((rc = layout_build(items, n, grad, Schedule(), &P->L, roomy))) { plan_free(P); return rc; }
+    for (Room room : {ROOM_FULL, ROOM_LEAN, ROOM_LEAST}) {
+        if ((rc = layout_build(items, n, grad, Schedule(), &P->L, room))) { plan_free(P); return rc; }
         layout_add_order(P->L);
-        const bool retry = roomy;
-        if (retry && P->L.dev_bytes > WORKSPACE_CAP) continue;
+        if (room == ROOM_FULL && P->L.dev_bytes > WORKSPACE_CAP) continue;
         if (hipMalloc(&P->d_buf, std::max<size_t>(P->L.dev_bytes, 256)) == hipSuccess) break;
         (void)hipGetLastError();
         P->d_buf = nullptr;
-        if (retry) continue;
+        if (room == ROOM_FULL || (room == ROOM_LEAN && grad)) continue;
         plan_free(P);
         return fail(SRP_ERR_OOM, "plan device allocation failed");
     }
@@ -1088,12 +1211,12 @@ int plan_refill(PlanImpl *P, const srp_batch_item *items, int64_t n, bool *compa
     int rc = check_items(items, n, P->L.grad, P->bo);
     if (rc) return rc;
     Layout L2;
-    if ((rc = layout_build(items, n, P->L.grad, P->L.sch, &L2, P->L.roomy))) return rc;
+    if ((rc = layout_build(items, n, P->L.grad, P->L.sch, &L2, P->L.room))) return rc;
     if (P->L.ordered) layout_add_order(L2);
     const Layout &L = P->L;
     if (L2.n != L.n || L2.stage_bytes != L.stage_bytes || L2.dev_bytes > L.dev_bytes || L2.grid != L.grid ||
         L2.wb != L.wb || L2.count != L.count || L2.dir != L.dir || L2.max_grad_n != L.max_grad_n ||
-        L2.grad_n != L.grad_n || L2.chain_off != L.chain_off || L2.chunk_base != L.chunk_base ||
+        L2.grad_n != L.grad_n || L2.chain_off != L.chain_off || L2.pieces != L.pieces || L2.chunk_base != L.chunk_base ||
         L2.patch_base != L.patch_base || L2.o_patches != L.o_patches || L2.o_counts != L.o_counts ||
         L2.total_units != L.total_units || L2.fan_base != L.fan_base || L2.fan_grid != L.fan_grid ||
         L2.o_units != L.o_units || L2.fans_inline != L.fans_inline ||
@@ -1402,7 +1525,7 @@ int srp_eval_batch_noalloc(const srp_batch_item *items, int64_t n_items, srp_res
     if ((rc = layout_build(items, n_items, false, Schedule(), &L))) return rc;
     // (buffers that only buy speed only where they fit beside the whole grid's stacks)
     if ((L.dev_bytes > NOALLOC_SCRATCH_BYTES || L.stage_bytes > NOALLOC_STAGE_BYTES) &&
-        (rc = layout_build(items, n_items, false, Schedule(), &L, false)))
+        (rc = layout_build(items, n_items, false, Schedule(), &L, ROOM_LEAN)))
         return rc;
     if ((rc = layout_fit(&L, NOALLOC_SCRATCH_BYTES))) return rc;
     if (L.stage_bytes > NOALLOC_STAGE_BYTES)

@@ -598,7 +598,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
         const int64_t kc = c - cur_begin;
         const int N = D.n;
 
-        int64_t p0 = kc * D.ppc, p1 = min(p0 + D.ppc, D.n_patches);
+        int64_t p0 = D.patch0 + kc * D.ppc, p1 = min(p0 + D.ppc, D.n_patches);
         // (patch order and costs: only in the 2-wave build, which the ordered
         // launches use, so the batch builds keep their registers)
         constexpr bool ORDERED = WPE == 2;
@@ -851,7 +851,7 @@ __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(
     wave_lds_fence();
     const TraceCtx TC = trace_ctx(D);
     const int B = D.bounces, gK = D.n_nodes;
-    const int64_t p0 = kc * D.group + part * GROUP_PART, p1 = min(p0 + GROUP_PART, D.n_patches);
+    const int64_t p0 = D.patch0 + kc * D.group + part * GROUP_PART, p1 = min(p0 + GROUP_PART, D.n_patches);
     // the part's patches with hits (lane i looks at patch p0 + i)
     uint64_t visit = __ballot(mine && p0 + lane < p1 &&
                               patches[D.patch_base + max((int64_t)0, min(p0 + lane, D.n_patches - 1))].hits != 0);

@@ -218,7 +218,7 @@ struct alignas(64) EvalDesc {
     uint32_t *chain;        // adjoint: the pixels' hit chains, n_patches x (bounces + 1) x 64 words, or null
     int64_t n_groups;       // adjoint: gradient groups
     int64_t patch_base;     // first patch of this evaluation (partial sums are per patch)
-    int64_t n_patches;      // 4 * tiles_x * tiles_y
+    int64_t n_patches;      // 4 * tiles_x * tiles_y (of a piece: the patch after its last)
     int32_t tiles_y;        // 16-pixel tile rows
     int32_t n_diffuse;      // diffuse rays per emitting hit (0 = none)
     // optional outputs
@@ -245,6 +245,8 @@ struct alignas(64) EvalDesc {
     const ArtNode *art;     // K tree nodes
     PrimaryEval *prim;      // the image of this evaluation's instances: a PrimaryEval, then K PrimaryInst
     int32_t group;          // patches per gradient group
+    int32_t patch0;         // first patch: 0, or that of a piece of an evaluation whose hit chains do not
+                            // fit at once (whole groups; chain, grad_part and n_groups are then the piece's)
 };
 
 // The host writes these records and the kernels read them: both compilation
@@ -298,6 +300,8 @@ static_assert(offsetof(EvalDesc, n_clamped) == 368, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, planar) == 376, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, vis) == 392, "EvalDesc layout");
 static_assert(offsetof(EvalDesc, leaf_of) == 408, "EvalDesc layout");
+static_assert(offsetof(EvalDesc, patch0) == 436, "EvalDesc layout");
+static_assert(sizeof(EvalDesc) == 448, "EvalDesc layout");
 static_assert(sizeof(PatchOut) == 64, "PatchOut layout");
 static_assert(offsetof(PatchOut, f) == 0, "PatchOut layout");
 static_assert(offsetof(PatchOut, hits) == 48, "PatchOut layout");

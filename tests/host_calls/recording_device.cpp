@@ -178,10 +178,47 @@ int launch_primary(const EvalDesc *d, int n_evals, const uint64_t *, int tile, c
     note(PRIMARY, n_evals, with, tile, n_tiles);
     return 0;
 }
+// Hit chains of a gradient batch, as the kernels address them: the trace
+// marks the first and last word of every patch's chains with the patch's number
+// and fills its sums, the adjoint looks for the marks, fills its groups' partials
+// and notes them, and the reduction expects every group of every evaluation once
+// and the fillings whole.  (Batches of few enough patches to touch their memory.)
+constexpr int64_t MARKED_PATCHES = 1000000;
+std::map<const double *, int> g_groups;
+bool in_device(const void *p, size_t bytes) {
+    auto f = g_dev.upper_bound(const_cast<void *>(p));
+    if (f == g_dev.begin()) return false;
+    --f;
+    return (const char *)p + bytes <= (const char *)f->first + f->second;
+}
+uint32_t *chains_of(const EvalDesc &D, int64_t pt) { return D.chain + pt * (D.bounces + 1) * 64; }
+bool filled(const void *p, size_t bytes, unsigned char v) {
+    const unsigned char *b = (const unsigned char *)p;
+    return std::all_of(b, b + bytes, [v](unsigned char x) { return x == v; });
+}
+int64_t patches_of(const EvalDesc *d, int n) {
+    int64_t np = 0;
+    for (int k = 0; k < n; ++k) np += d[k].n_patches - d[k].patch0;
+    return np;
+}
 // TRACE: evaluations, chunks, fans traced inside, fan units listed
-int launch_trace(const EvalDesc *, const int64_t *, int n_evals, const uint64_t *, int64_t total_chunks, uint32_t *,
-                 uint32_t *, PatchOut *, uint64_t *, bool, int, PatchOut *d_fan_out, uint64_t *, bool fans_inline,
-                 int4 *d_fan_units, int, const uint32_t *, uint32_t *, void *) {
+int launch_trace(const EvalDesc *d, const int64_t *chunk_base, int n_evals, const uint64_t *, int64_t total_chunks,
+                 uint32_t *, uint32_t *, PatchOut *patches, uint64_t *, bool, int, PatchOut *d_fan_out, uint64_t *,
+                 bool fans_inline, int4 *d_fan_units, int, const uint32_t *, uint32_t *, void *) {
+    int64_t at = 0;
+    for (int k = 0; k < n_evals; ++k) {
+        if (chunk_base[k] != at) ++g_faults;
+        at += (d[k].n_patches - d[k].patch0 + d[k].ppc - 1) / d[k].ppc;
+    }
+    if (chunk_base[n_evals] != at || total_chunks != at) ++g_faults;
+    if (n_evals > 0 && d[0].chain && patches_of(d, n_evals) <= MARKED_PATCHES)
+        for (int k = 0; k < n_evals; ++k)
+            for (int64_t pt = d[k].patch0; pt < d[k].n_patches; ++pt) {
+                uint32_t *c = chains_of(d[k], pt);
+                if (!in_device(c, 256 * (size_t)(d[k].bounces + 1))) { ++g_faults; continue; }
+                c[0] = c[64 * (d[k].bounces + 1) - 1] = (uint32_t)(d[k].patch_base + pt) + 1u;
+                std::memset((void *)&patches[d[k].patch_base + pt], 0xEE, sizeof(PatchOut));
+            }
     note(TRACE, n_evals, total_chunks, d_fan_out && fans_inline, d_fan_units != nullptr);
     return 0;
 }
@@ -191,8 +228,20 @@ int launch_adjoint(const EvalDesc *d, int n_evals, const uint32_t *block_base, u
     for (int k = 0; k < n_evals; ++k) {
         const int64_t nb = block_base[k + 1] - block_base[k], parts = d[k].group / GROUP_PART;
         if (nb * block_waves < d[k].n_groups * parts || (nb - 1) * block_waves >= d[k].n_groups * parts) ++g_faults;
-        if (parts < 1 || parts > block_waves || d[k].n_groups * d[k].group < d[k].n_patches) ++g_faults;
+        if (parts < 1 || parts > block_waves) ++g_faults;
+        if (d[k].patch0 % d[k].group || d[k].n_groups * d[k].group < d[k].n_patches - d[k].patch0) ++g_faults;
     }
+    if (patches_of(d, n_evals) <= MARKED_PATCHES)
+        for (int k = 0; k < n_evals; ++k)
+            for (int64_t g = 0; g < d[k].n_groups; ++g) {
+                ++g_groups[d[k].grad_part + g * d[k].grad_n];
+                if (!in_device(d[k].grad_part + g * d[k].grad_n, sizeof(double) * d[k].grad_n)) { ++g_faults; continue; }
+                std::memset((void *)(d[k].grad_part + g * d[k].grad_n), 0xDD, sizeof(double) * d[k].grad_n);
+                const int64_t p0 = d[k].patch0 + g * d[k].group;
+                for (int64_t pt = p0; pt < std::min<int64_t>(p0 + d[k].group, d[k].n_patches); ++pt)
+                    for (int w : {0, 64 * (d[k].bounces + 1) - 1})
+                        if (chains_of(d[k], pt)[w] != (uint32_t)(d[k].patch_base + pt) + 1u) ++g_faults;
+            }
     check_owners(block_base, n_evals, n_blocks, max_blocks);
     note(ADJOINT, n_evals, n_blocks, block_waves);
     return 0;
@@ -203,11 +252,24 @@ int launch_fans(const EvalDesc *, const uint64_t *, int64_t max_units, uint32_t 
     return 0;
 }
 // REDUCE: evaluations, range sums; a missing result buffer is a fault
-int launch_reduce(const EvalDesc *, int n_evals, const uint64_t *, const PatchOut *, const uint64_t *, const PatchOut *,
-                  const uint64_t *, bool, bool, const uint32_t *, int64_t total_slices, void *d_out, uint32_t *,
+int launch_reduce(const EvalDesc *d, int n_evals, const uint64_t *, const PatchOut *patches, const uint64_t *, const PatchOut *,
+                  const uint64_t *, bool, bool grad, const uint32_t *, int64_t total_slices, void *d_out, uint32_t *,
                   const uint32_t *, uint32_t *, void *) {
     note(REDUCE, n_evals, total_slices);
     if (!d_out) ++g_faults;
+    if (grad && !g_groups.empty()) {
+        int64_t want = 0;
+        for (int k = 0; k < n_evals; ++k) {
+            want += d[k].n_groups;
+            for (int64_t g = 0; g < d[k].n_groups; ++g) {
+                const double *part = d[k].grad_part + g * d[k].grad_n;
+                if (g_groups[part] != 1 || !filled(part, sizeof(double) * d[k].grad_n, 0xDD)) ++g_faults;
+            }
+            if (!filled(patches + d[k].patch_base, sizeof(PatchOut) * d[k].n_patches, 0xEE)) ++g_faults;
+        }
+        if ((int64_t)g_groups.size() != want) ++g_faults;
+    }
+    g_groups.clear();
     return 0;
 }
 int trace_blocks_per_cu(bool) { return 4; }

@@ -99,9 +99,19 @@ class Device:
 
 
 @pytest.fixture
-def dev(so, tmp_path):
-    shutil.copy(so, tmp_path / "lib.so")   # (a library of another path is loaded, and starts, anew)
-    return Device(tmp_path / "lib.so")
+def devices(so, tmp_path):
+    def fresh():
+        fresh.n += 1
+        p = tmp_path / f"lib{fresh.n}.so"
+        shutil.copy(so, p)   # (a library of another path is loaded, and starts, anew)
+        return Device(p)
+    fresh.n = 0
+    return fresh
+
+
+@pytest.fixture
+def dev(devices):
+    return devices()
 
 
 SUN = (0.3, -0.5, 0.8)
@@ -178,3 +188,58 @@ def test_launches_are_numbered_through_uneven_batches(dev, small):
     assert primary[0][2] == len(with_vis) and primary[0][4] == sum(_tiles(p.n, px) for _, p in with_vis)
     patches = [4 * (-(-p.n // 16)) ** 2 for _, p in entries]
     assert adjoint[0][2] <= sum(-(-k // 8) for k in patches) and dev.lib.dev_faults() == 0
+
+
+def _patches(n):
+    return 4 * (-(-n // 16)) ** 2
+
+
+@pytest.mark.parametrize("plan", [False, True])
+@pytest.mark.parametrize("bounces,ppc", [(0, 1), (2, 5), (4, 64)])
+def test_gradients_without_room_for_their_chains(devices, plan, bounces, ppc):
+    """A gradient batch whose hit chains do not fit the device's free memory runs
+    them a window after the other, eager and captured: evaluations are cut at gradient
+    groups (of 8 to 64 patches here), every group is swept once, from the chains of its
+    own patches, and no chain lies outside the workspace."""
+    many = synth.greebled_spacecraft(seed=3, bus_n=8, n_greebles=20, seg_nx=3, seg_ny=4)
+    sizes = [(many, 2000), (synth.box_wing(), 33), (many, 1000), (synth.box_wing(), 700), (many, 100), (many, 1)]
+    chains = sum(256 * (bounces + 1) * _patches(n) for _, n in sizes)
+    hits = sum(520 * _patches(n) for m, n in sizes if m is many and n > 100)
+
+    def run(limit):
+        dev = devices()
+        scenes = {id(m): dev.scene(m) for m, _ in sizes}
+        entries = [(scenes[id(m)], params(SUN, n, bounces)) for m, n in sizes]
+        dev.lib.srp_set_schedule(ppc, 4)
+        dev.lib.dev_limit(limit)
+        before = dev.lib.dev_used()
+        if plan:
+            arr, h = dev.items(entries), C.c_void_p()
+            assert dev.lib.srp_plan_create(arr, len(arr), L.SRP_PLAN_GRAD, 1 << 20, 1 << 20, 1 << 20, C.byref(h)) == 0, \
+                dev.error()
+            assert dev.lib.srp_plan_update(h, arr, len(arr)) == 0, dev.error()
+        else:
+            assert dev.batch(entries, grad=True) == 0, dev.error()
+        assert dev.lib.dev_faults() == 0
+        return dev.lib.dev_used() - before, sum(r[0] == "adjoint" for r in dev.log())
+
+    need, sweeps = run(-1)
+    assert sweeps == 1
+    need, sweeps = run(need - chains - hits + (6 << 20))
+    assert sweeps >= chains // (4 << 20) > 1
+
+
+def test_large_captured_gradient_batches_hold_a_part_of_their_chains(devices):
+    """A captured batch is not split at the workspace cap: beyond it the rasterised hits
+    are left out, and at most 1 GiB of chains is held at a time."""
+    dev = devices()
+    sc = dev.scene(synth.icosphere(subdiv=2))
+    entries = [(sc, params(SUN, 2048, 4))] * 150
+    arr, h = dev.items(entries), C.c_void_p()
+    before = dev.lib.dev_used()
+    assert dev.lib.srp_plan_create(arr, len(arr), L.SRP_PLAN_GRAD, 1 << 20, 1 << 20, 1 << 20, C.byref(h)) == 0, dev.error()
+    log = dev.log()
+    chains = 150 * 65536 * 256 * 5
+    assert sum(r[0] == "adjoint" for r in log) == -(-chains // (1 << 30)) and dev.lib.dev_faults() == 0
+    assert sum(r[1] for r in log if r[0] == "trace") == 150 + -(-chains // (1 << 30)) - 1   # (cut where a window ends)
+    assert dev.lib.dev_used() - before < 4 << 30
