@@ -739,8 +739,11 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     for (ChainPiece &pc : L.pieces) pc.off += goff;
     goff = align_up(goff + window_bytes);
     for (int64_t k = 0; k < n; ++k) {
-        L.pslice_off[k] = goff;
-        goff = align_up(goff + sizeof(SliceOut) * L.n_slices[k]);
+        // (an evaluation with fans has more range sums than its patches alone would: they
+        // lie on its emitter records, which the fans have read by then)
+        static_assert(sizeof(SliceOut) * MAX_SLICES <= sizeof(FanRec) * 64 * 4, "an evaluation has at least 4 patches");
+        L.pslice_off[k] = L.emit_off[k] ? L.emit_off[k] : goff;
+        if (!L.emit_off[k]) goff = align_up(goff + sizeof(SliceOut) * L.n_slices[k]);
         if (!grad) continue;
         L.chain_off[k] = goff;
         if (L.pieces.empty()) goff = align_up(goff + patch_chain(k) * (L.patch_base[k + 1] - L.patch_base[k]));

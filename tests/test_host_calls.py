@@ -243,3 +243,16 @@ def test_large_captured_gradient_batches_hold_a_part_of_their_chains(devices):
     assert sum(r[0] == "adjoint" for r in log) == -(-chains // (1 << 30)) and dev.lib.dev_faults() == 0
     assert sum(r[1] for r in log if r[0] == "trace") == 150 + -(-chains // (1 << 30)) - 1   # (cut where a window ends)
     assert dev.lib.dev_used() - before < 4 << 30
+
+
+@pytest.mark.parametrize("sizes,bounces,diffuse", [((112, 688), 3, 19), ((368, 592), 3, 20), ((400, 480), 3, 37),
+                                                   ((144, 608), 3, 38)])
+def test_the_fixed_workspace_holds_what_patch_counted_range_sums_left(dev, sizes, bounces, diffuse):
+    """Diffuse batches within a few hundred bytes of the fixed workspace, which
+    held them with one range sum per 1,024 patches: those counted by fan passes
+    as well (16 here) must not push them out."""
+    sc = dev.scene(synth.box_wing())
+    entries = [(sc, params(SUN, n, bounces, diffuse=diffuse)) for n in sizes]
+    assert dev.batch(entries, noalloc=True) == 0, dev.error()
+    log = dev.log()
+    assert log[-1][0] == "reduce" and log[-1][2] > sum(max(1, _patches(n) // 1024) for n in sizes)
