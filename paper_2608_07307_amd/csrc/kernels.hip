@@ -350,19 +350,13 @@ __device__ __forceinline__ void fan_dir(const float n[3], const float4 l, float 
 // (Item numbers stay below 2^31 and are 32-bit here: the scalar unit has no
 // 64-bit order compare, and 64-bit ones cost the batch kernels 14 spilled
 // registers and 6 % of the forward launch.)
+// A trace launch of one item per wave at most asks no counter (own_items): 32 waves of
+// each counter took 10 us of a launch over 2,048 patches of the box-wing (28 us, now 18).
 struct WorkQueue {
-    uint32_t r;          // the queue
+    uint32_t r;          // the queue (N_QUEUES: none, the wave has item `at` only)
     uint32_t at, seen;   // its next position of this wave; its counter as last known (the run's end)
 };
 constexpr uint32_t NO_ITEM = 0xFFFFFFFFu;
-
-// Position i of queue r: one of the i-th N_QUEUES consecutive items, a
-// different one at every position, so that a run of positions samples the
-// whole image (a fixed one would follow one image column wherever a row of the
-// image holds a multiple of N_QUEUES items: 8.1 ms in place of 3.5).
-__device__ __forceinline__ uint32_t queue_item(uint32_t i, uint32_t r) {
-    return i * N_QUEUES + ((r + i * 37u) & (N_QUEUES - 1));
-}
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
@@ -376,18 +370,30 @@ __device__ __forceinline__ WorkQueue work_queue(int wv) {
     return q;
 }
 
+// The same for a launch of `total` items, each of them its wave's own where own_items says so.
+__device__ __forceinline__ WorkQueue work_queue(int wv, uint32_t total, int grid_blocks) {
+    WorkQueue q = work_queue(wv);
+    if (own_items(total, (uint32_t)grid_blocks)) {
+        q.r = N_QUEUES;
+        q.at = uniform_u32(own_item(blockIdx.x, (uint32_t)wv, (uint32_t)grid_blocks));
+    }
+    return q;
+}
+
 // The next of `total` work items, or NO_ITEM once every queue is drained.
 // Lane 0 talks to the queue's counter and broadcasts, so the result is
 // wave-uniform.
 __device__ __forceinline__ uint32_t take_work(WorkQueue &q, uint32_t *counters, uint32_t total, int grid_blocks,
                                               int lane) {
-    const uint32_t n_r = (total + N_QUEUES - 1) / N_QUEUES;   // positions of each queue
+    if (q.r == N_QUEUES) {
+        const uint32_t c = q.at < total ? q.at : NO_ITEM;
+        q.at = NO_ITEM;
+        return c;
+    }
     #pragma unroll 1
     for (;;) {
-        while (q.at < q.seen && q.at < n_r) {
-            const uint32_t c = queue_item(q.at++, q.r);
-            if (c < total) return c;
-        }
+        const uint32_t n_r = queue_positions(total, q.r);
+        if (q.at < q.seen && q.at < n_r) return queue_item(q.at++, q.r, total);
         if (q.seen < n_r) {
             // (n is at most a fourth of what is left, so a counter stays far below 2^32)
             const int share = 33 - __clz(max(1, grid_blocks * (BLOCK / WAVE) / N_QUEUES));
@@ -400,7 +406,7 @@ __device__ __forceinline__ uint32_t take_work(WorkQueue &q, uint32_t *counters, 
         }
         // drained: look at every queue's counter at once, one per lane
         const uint32_t c = __hip_atomic_load(counters + lane * QUEUE_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t open = __ballot(c < n_r);
+        const uint64_t open = __ballot(c < queue_positions(total, (uint32_t)lane));
         if (!open) return NO_ITEM;
         // the next open one after r
         const uint64_t above = open & (q.r < N_QUEUES - 1 ? ~0ull << (q.r + 1) : 0ull);
@@ -557,7 +563,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
     // until all are drained, with no block barrier.  Every queue walks the whole
     // batch in order, so expensive image regions spread over the grid and over
     // time.
-    WorkQueue wq = work_queue(wv);
+    WorkQueue wq = work_queue(wv, (uint32_t)total_chunks, grid_blocks);
     int cur = -1;                          // evaluation of the previous chunk
     uint32_t cur_begin = 0, cur_end = 0;   // its chunk range
     // its ray grid: origin o0, steps su and sv, direction dd (3 floats each, a float4

@@ -340,6 +340,34 @@ constexpr int N_QUEUES = 64;      // (one lane per counter when a wave looks at 
 constexpr int QUEUE_STRIDE = 8;   // (128-byte spacing measured the same)
 constexpr int FAN_UNITS_AT = 2 * N_QUEUES * QUEUE_STRIDE;
 constexpr int QUEUE_WORDS = FAN_UNITS_AT + 64;
+// The items of queue r: one of every N_QUEUES consecutive ones, a different one at
+// every position i, so that a run of positions samples the whole image (a fixed one
+// would follow one image column wherever a row of the image holds a multiple of
+// N_QUEUES items: 8.1 ms in place of 3.5), and of the rest item r, so that the number of
+// positions is plain.  (Exact, for a wave asks every queue that seems to hold
+// items: with a position for every queue in the rest, a launch of 4 chunks asked up
+// to 60 empty queues one by one, 20 us of a 77 us call.)
+SRP_HD inline uint32_t queue_positions(uint32_t total, uint32_t r) { return (total + N_QUEUES - 1 - r) / N_QUEUES; }
+SRP_HD inline uint32_t queue_item(uint32_t i, uint32_t r, uint32_t total) {
+    const uint32_t skew = i < total / N_QUEUES ? i * 37u : 0u;
+    return i * N_QUEUES + ((r + skew) & (N_QUEUES - 1));
+}
+// Whether each of `total` items belongs to a wave of its own, and which: the waves
+// suffice, and there is a block for every compute unit.  (A smaller launch ends on the
+// compute unit that holds most of its long patches, which a queue spreads: the 36
+// patches of one 33^2 image of the 50k craft 69 us by queues, 71-75 us so; a batch of eight
+// 128^2 images 140 us by queues, 128 so.)  Neighbouring items, and the heaviest ones of an
+// ordered launch's evaluations, go to different blocks: the blocks' first waves take the
+// first items, their second waves the next ones, from another block on (from the same
+// block on, a captured batch of eight 128^2 images of 200k triangles took 240 us, by
+// queues 220, so 211).
+constexpr uint32_t OWN_ITEM_BLOCKS = 256;   // the MI355X's compute units
+SRP_HD inline bool own_items(uint32_t total, uint32_t blocks) {
+    return blocks >= OWN_ITEM_BLOCKS && total <= blocks * (BLOCK / 64);
+}
+SRP_HD inline uint32_t own_item(uint32_t block, uint32_t wave, uint32_t blocks) {
+    return wave * blocks + (block + wave * 101u) % blocks;
+}
 // Copies bytes (a multiple of 16) of pinned host memory to the device by a kernel.
 int launch_upload(char *dst, const char *src, size_t bytes, void *stream);
 int launch_window(const EvalDesc *d_desc, int n_evals, int blocks_x, uint64_t *d_win, uint32_t *d_queue,

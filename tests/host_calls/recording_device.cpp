@@ -49,6 +49,27 @@ int64_t dev_log(int64_t *out, int64_t cap) {
     return (int64_t)g_log.size();
 }
 
+// Whether the queues hand out every one of `total` items once, and `blocks` blocks of
+// own items do where own_items allows it.
+int queue_faults(uint32_t total, uint32_t blocks) {
+    int faults = 0;
+    std::vector<int> seen(total, 0);
+    for (uint32_t r = 0; r < N_QUEUES; ++r)
+        for (uint32_t i = 0; i < queue_positions(total, r); ++i) {
+            const uint32_t c = queue_item(i, r, total);
+            if (c >= total || seen[c]++) ++faults;
+        }
+    faults += (int)std::count(seen.begin(), seen.end(), 0);
+    if (!own_items(total, blocks)) return faults;
+    std::fill(seen.begin(), seen.end(), 0);
+    for (uint32_t b = 0; b < blocks; ++b)
+        for (uint32_t w = 0; w < BLOCK / 64; ++w) {
+            const uint32_t c = own_item(b, w, blocks);
+            if (c < total && seen[c]++) ++faults;
+        }
+    return faults + (int)std::count(seen.begin(), seen.end(), 0);
+}
+
 hipError_t hipMalloc(void **p, size_t n) {
     *p = nullptr;
     if (g_used + n > g_limit) return hipErrorOutOfMemory;

@@ -256,3 +256,14 @@ def test_the_fixed_workspace_holds_what_patch_counted_range_sums_left(dev, sizes
     assert dev.batch(entries, noalloc=True) == 0, dev.error()
     log = dev.log()
     assert log[-1][0] == "reduce" and log[-1][2] > sum(max(1, _patches(n) // 1024) for n in sizes)
+
+
+def test_queues_hold_every_item_and_nothing_else(dev):
+    """Every item of a launch is at exactly one position of one queue, no queue counts
+    a position without an item (a wave would ask it in vain), and where waves have
+    items of their own every item has its wave."""
+    totals = list(range(300)) + [64 * k + d for k in (16, 64, 1000) for d in (-1, 0, 1, 37, 63)]
+    assert [t for t in totals if dev.lib.queue_faults(t, 1)] == []
+    for blocks in (255, 256, 257, 300, 511, 512, 1024):
+        for total in (1, 255, 256, 1000, 1024, 4 * blocks - 1, 4 * blocks, 4 * blocks + 1):
+            assert dev.lib.queue_faults(total, blocks) == 0, (total, blocks)
