@@ -471,6 +471,21 @@ constexpr int64_t RASTER_MIN_PATCHES = 16384, RASTER_BIG_PATCHES = 131072;
 // with 32), larger ones repeat less work (1024^2 x 64 of 50k: 3.07, 2.57 and 3.6 ms).
 int raster_tile(int64_t patches) { return patches >= RASTER_BIG_PATCHES ? 16 : 8; }
 
+// A tile is one wave's, which tests its triangles at about 50 ns each, and the launch waits
+// for the fullest tile.  So images that crowd more than 0.12 triangles per patch of
+// the launch (half of what the traversal takes for the launch, 13 ns per patch) or
+// 15,000 into a tile keep the traversal.  Measured at B = 1, traversal / rasterised, us,
+// spheres of 81,920 and 327,680 triangles on booms of 20 and 60 times their radius (most
+// triangles in a tile, patches of the launch): 18k, 131k 640 / 1,170, with gradients 680 /
+// 1,210; 18k, 524k 1,120 / 2,520; 24k, 262k 920 / 1,590; 24k, 1M 1,890 / 3,270; 170k, 524k
+// 910 / 2,960; 49k, 262k 650 / 2,220; but 6k, 1M 3,220 / 1,650 and 6k, 131k 960 / 590.
+// The 2k to 200k crafts, at 0.002 to 0.07 triangles per patch and at most 11k, gain.
+bool crowded(const srp_batch_item &it, int tile, int64_t patches) {
+    const int k = std::min(std::max(ilog2(it.p.n / tile), 0), CROWD_LEVELS - 1);   // (cells of a tile or more)
+    const double crowd = it.scene->h.crowd[k];
+    return crowd > 15000.0 || crowd > 0.12 * (double)patches;
+}
+
 int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule force, Layout *Lp,
                  Room room = ROOM_FULL) {
     Layout &L = *Lp;
@@ -638,13 +653,15 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
             L.vis_patches = 0;
             if (least == RASTER_BIG_PATCHES) ratio = 0.25;
         }
+        const int64_t patches = L.vis_patches;
         int64_t at = 0;
-        for (int64_t k = 0; k < n && L.vis_patches > 0; ++k) {
-            if (!use_raster(items[k], ratio)) continue;
+        for (int64_t k = 0; k < n && patches > 0; ++k) {
+            if (!use_raster(items[k], ratio) || crowded(items[k], raster_tile(patches), patches)) continue;
             L.item_vis[k] = 1;
             L.vis_base[k] = at;
             at += L.patch_base[k + 1] - L.patch_base[k];
         }
+        L.vis_patches = at;
     }
     if (L.vis_patches > 0) {
         L.vis_tile = raster_tile(L.vis_patches);

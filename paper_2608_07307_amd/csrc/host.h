@@ -54,6 +54,8 @@ struct SlotLayout {
 SlotLayout slot_layout(int n_nodes, int n_tlas, int n_dof);
 void slot_pack(const SlotHost &s, const SlotLayout &L, char *dst);
 
+constexpr int CROWD_LEVELS = 10;
+constexpr size_t CROWD_MIN_TRIS = 1500;   // scenes of fewer triangles are not counted: all of them at every level
 struct SceneHost {
     int32_t n_nodes = 0, n_mats = 0, n_dof = 0;
     int64_t n_tris = 0;
@@ -65,6 +67,7 @@ struct SceneHost {
     std::vector<int32_t> parent;
     std::vector<PlateLocal> plates; // N-plate model, in the order of each plate's first triangle
     double pad = 0;                 // box padding (metres)
+    int32_t crowd[CROWD_LEVELS] = {0};   // about the most triangles in a square of 2^-k the craft's extent, seen obliquely
     int max_blas_depth = 0;
     // top level: 4-wide nodes over the non-empty nodes' instances, built once over
     // the rest pose; a slot copies the references and refits the boxes (children

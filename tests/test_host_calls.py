@@ -267,3 +267,41 @@ def test_queues_hold_every_item_and_nothing_else(dev):
     for blocks in (255, 256, 257, 300, 511, 512, 1024):
         for total in (1, 255, 256, 1000, 1024, 4 * blocks - 1, 4 * blocks, 4 * blocks + 1):
             assert dev.lib.queue_faults(total, blocks) == 0, (total, blocks)
+
+
+def _on_booms(subdiv, length):
+    """A sphere of 20 x 4^subdiv triangles and six bare booms of `length` times its radius."""
+    s = synth.icosphere(subdiv=subdiv)
+    L, w = length, 0.02
+    parts = [s] + [synth.plate(o, u, v, nu=4, nv=1) for o, u, v in (
+        ((-L, -w, 0), (2 * L, 0, 0), (0, 2 * w, 0)), ((-w, 0, -L), (0, 0, 2 * L), (2 * w, 0, 0)),
+        ((0, -L, -w), (0, 2 * L, 0), (0, 0, 2 * w)))]
+    at = np.cumsum([0] + [len(p.verts) for p in parts])
+    s.tris = np.concatenate([p.tris + a for p, a in zip(parts, at)]).astype(np.int32)
+    s.verts = np.concatenate([p.verts for p in parts])
+    s.tri_mat, s.tri_node = np.zeros(len(s.tris), np.int32), np.zeros(len(s.tris), np.int32)
+    return s
+
+
+@pytest.mark.parametrize("mesh,n,items,rasterised", [
+    ("crowded", 512, 32, False),     # 81,920 triangles on a few tiles, 0.31 per pixel of the whole image
+    ("crowded", 1024, 64, True),     # the same body over some dozen tiles of a launch of a million patches
+    ("crowded", 2048, 1, True),      # and over more of them in one fine image
+    ("even", 512, 64, True),         # as many triangles all over the image
+    ("craft", 300, 648, True),
+    ("craft", 1024, 64, True),
+    ("craft", 512, 8, True),
+    ("small craft", 128, 64, True),
+])
+def test_images_with_crowded_tiles_keep_the_traversal(dev, mesh, n, items, rasterised):
+    m = {"crowded": lambda: _on_booms(6, 20), "even": lambda: synth.icosphere(subdiv=6),
+         "craft": lambda: synth.procedural_sized(3, 50000), "small craft": lambda: synth.procedural_sized(3, 3000)}[mesh]()
+    sc, other = dev.scene(m), dev.scene(_grid_mesh(2000))
+    rng = np.random.default_rng(1)
+    assert dev.batch([(sc, params(s, n, 1)) for s in rng.normal(size=(items, 3))]) == 0, dev.error()
+    got = [r for r in dev.log() if r[0] == "primary"]
+    assert [r[2] for r in got] == ([items] if rasterised else [])
+    # an image beside it that is not crowded is rasterised in either case
+    assert dev.batch([(sc, params(SUN, n, 1))] * items + [(other, params(SUN, 1024, 1))]) == 0, dev.error()
+    got = [r for r in dev.log() if r[0] == "primary"]
+    assert [r[2] for r in got] == [items + 1 if rasterised else 1] and dev.lib.dev_faults() == 0
