@@ -67,6 +67,7 @@ struct SceneHost {
     std::vector<int32_t> parent;
     std::vector<PlateLocal> plates; // N-plate model, in the order of each plate's first triangle
     double pad = 0;                 // box padding (metres)
+    double layers = 0;              // surfaces over one another, on average over its extent seen obliquely
     int32_t crowd[CROWD_LEVELS] = {0};   // about the most triangles in a square of 2^-k the craft's extent, seen obliquely
     int max_blas_depth = 0;
     // top level: 4-wide nodes over the non-empty nodes' instances, built once over

@@ -693,7 +693,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
                     #pragma unroll 1
                     for (;;) {
                         Hit h;
-                        if (seen && gen == 0) {
+                        if (seen && gen == 0 && first.y != VIS_UNKNOWN) {
                             h.t = __uint_as_float(first.x);
                             h.tri = (int32_t)first.y;
                             const TriRec SRP_GLOBAL &T = TC.tris[h.tri];

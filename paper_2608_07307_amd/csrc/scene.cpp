@@ -302,27 +302,35 @@ bool finite3(const double *v) { return std::isfinite(v[0]) && std::isfinite(v[1]
 // cells, which few Sun directions see (of the 50k craft's triangles 5,100 in a cell of a
 // 64th of its extent so, 1,800 obliquely).  Fine cells only where triangles are many (1 ms of
 // the 2 ms that a scene of 2,000 triangles takes to build, else 2 of 37 for 50k).
-void crowd_levels(const std::vector<TriRec> &rec, int32_t *out) {
+// layers: the triangles' area in the three images over that of the squares.
+void crowd_levels(const std::vector<TriRec> &rec, int32_t *out, double *layers) {
     for (int k = 0; k < CROWD_LEVELS; ++k) out[k] = (int32_t)rec.size();
-    if (rec.size() < CROWD_MIN_TRIS) return;
+    *layers = 0;
     const double R[3][3] = {{2.0 / 3, 1.0 / 3, 2.0 / 3}, {-2.0 / 3, 2.0 / 3, 1.0 / 3}, {-1.0 / 3, -2.0 / 3, 2.0 / 3}};
     const size_t n = rec.size();
     std::vector<float> x(3 * n);
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, area = 0;
     for (size_t i = 0; i < n; ++i) {
         const TriRec &t = rec[i];
+        double p[3][3];
         for (int a = 0; a < 3; ++a) {
-            double c = 0;
+            int k = 0;
             for (const float *v : {t.v0, t.v1, t.v2}) {
-                const double p = R[a][0] * v[0] + R[a][1] * v[1] + R[a][2] * v[2];
-                lo[a] = std::min(lo[a], p);
-                hi[a] = std::max(hi[a], p);
-                c += p / 3;
+                p[k][a] = R[a][0] * v[0] + R[a][1] * v[1] + R[a][2] * v[2];
+                lo[a] = std::min(lo[a], p[k][a]);
+                hi[a] = std::max(hi[a], p[k][a]);
+                ++k;
             }
-            x[3 * i + a] = (float)c;
+            x[3 * i + a] = (float)((p[0][a] + p[1][a] + p[2][a]) / 3);
+        }
+        for (int a = 0; a < 3; ++a) {
+            const int b = (a + 1) % 3;
+            area += 0.5 * std::fabs((p[1][a] - p[0][a]) * (p[2][b] - p[0][b]) - (p[2][a] - p[0][a]) * (p[1][b] - p[0][b]));
         }
     }
     const double extent = std::max(hi[0] - lo[0], std::max(hi[1] - lo[1], hi[2] - lo[2]));
+    if (extent > 0) *layers = area / (3 * extent * extent);
+    if (n < CROWD_MIN_TRIS) return;
     const int top = n < 16384 ? 7 : CROWD_LEVELS - 1, SIDE = 1 << top;
     // (a fifth wider than the craft and off its middle, where a body on symmetric booms
     // would be shared by four cells at every level)
@@ -466,7 +474,7 @@ int scene_build(const double *verts, int64_t n_verts, const int32_t *tris, int64
         nn[2] += e1[0] * e2[1] - e1[1] * e2[0];
     }
     S->pad = 4e-6 * scale + 1e-9;
-    crowd_levels(rec, S->crowd);
+    crowd_levels(rec, S->crowd, &S->layers);
     for (auto &nd : S->nodes) {
         double l = std::sqrt(nd.n0[0] * nd.n0[0] + nd.n0[1] * nd.n0[1] + nd.n0[2] * nd.n0[2]);
         for (int a = 0; a < 3; ++a) nd.n0[a] = l > 0 ? nd.n0[a] / l : 0.0;

@@ -189,6 +189,8 @@ struct alignas(64) PrimaryInst {
 };
 static_assert(sizeof(PrimaryInst) == 192, "PrimaryInst layout");
 
+constexpr uint32_t VIS_UNKNOWN = 0xFFFFFFFFu;
+
 // One evaluation, as the kernels see it.
 struct alignas(64) EvalDesc {
     // scene
@@ -239,8 +241,9 @@ struct alignas(64) EvalDesc {
     float box_pad;          // padding of the hierarchies' boxes (metres)
     uint64_t planar[2];     // bit k: every triangle of node k lies in one plane (rays leaving it skip it)
     // primary hits by k_primary (null: the trace kernel traces the primary rays)
-    uint2 *vis;             // n_patches x 64: distance bits, leaf-order triangle (where the mask is set)
-    uint64_t *vis_mask;     // n_patches: the patch's hit pixels
+    uint2 *vis;             // n_patches x 64: distance bits, leaf-order triangle (where the mask is set), or
+                            // VIS_UNKNOWN for the triangle: the trace kernel traces the primary ray
+    uint64_t *vis_mask;     // n_patches: the patch's pixels that hit, or that are not known to miss
     const int32_t *leaf_of; // T: leaf-order index of an original triangle index
     const ArtNode *art;     // K tree nodes
     PrimaryEval *prim;      // the image of this evaluation's instances: a PrimaryEval, then K PrimaryInst

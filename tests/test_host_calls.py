@@ -269,6 +269,16 @@ def test_queues_hold_every_item_and_nothing_else(dev):
             assert dev.lib.queue_faults(total, blocks) == 0, (total, blocks)
 
 
+def _merged(parts):
+    """One rigid body of several meshes."""
+    m = synth.icosphere(subdiv=0)
+    at = np.cumsum([0] + [len(p.verts) for p in parts])
+    m.tris = np.concatenate([p.tris + a for p, a in zip(parts, at)]).astype(np.int32)
+    m.verts = np.concatenate([p.verts for p in parts])
+    m.tri_mat, m.tri_node = np.zeros(len(m.tris), np.int32), np.zeros(len(m.tris), np.int32)
+    return m
+
+
 def _on_booms(subdiv, length):
     """A sphere of 20 x 4^subdiv triangles and six bare booms of `length` times its radius."""
     s = synth.icosphere(subdiv=subdiv)
@@ -276,11 +286,7 @@ def _on_booms(subdiv, length):
     parts = [s] + [synth.plate(o, u, v, nu=4, nv=1) for o, u, v in (
         ((-L, -w, 0), (2 * L, 0, 0), (0, 2 * w, 0)), ((-w, 0, -L), (0, 0, 2 * L), (2 * w, 0, 0)),
         ((0, -L, -w), (0, 2 * L, 0), (0, 0, 2 * w)))]
-    at = np.cumsum([0] + [len(p.verts) for p in parts])
-    s.tris = np.concatenate([p.tris + a for p, a in zip(parts, at)]).astype(np.int32)
-    s.verts = np.concatenate([p.verts for p in parts])
-    s.tri_mat, s.tri_node = np.zeros(len(s.tris), np.int32), np.zeros(len(s.tris), np.int32)
-    return s
+    return _merged(parts)
 
 
 @pytest.mark.parametrize("mesh,n,items,rasterised", [
@@ -292,9 +298,11 @@ def _on_booms(subdiv, length):
     ("craft", 1024, 64, True),
     ("craft", 512, 8, True),
     ("small craft", 128, 64, True),
+    ("plates", 512, 64, False),      # 200 layers, few triangles in any tile
 ])
 def test_images_with_crowded_tiles_keep_the_traversal(dev, mesh, n, items, rasterised):
     m = {"crowded": lambda: _on_booms(6, 20), "even": lambda: synth.icosphere(subdiv=6),
+         "plates": lambda: _merged([synth.plate((-1, -1, k / 100 - 1), (2, 0, 0), (0, 2, 0), nu=4, nv=4) for k in range(200)]),
          "craft": lambda: synth.procedural_sized(3, 50000), "small craft": lambda: synth.procedural_sized(3, 3000)}[mesh]()
     sc, other = dev.scene(m), dev.scene(_grid_mesh(2000))
     rng = np.random.default_rng(1)
