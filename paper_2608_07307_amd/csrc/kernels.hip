@@ -384,7 +384,7 @@ __device__ __forceinline__ WorkQueue work_queue(int wv, uint32_t total, int grid
 // Lane 0 talks to the queue's counter and broadcasts, so the result is
 // wave-uniform.
 __device__ __forceinline__ uint32_t take_work(WorkQueue &q, uint32_t *counters, uint32_t total, int grid_blocks,
-                                              int lane) {
+                                              bool single, int lane) {
     if (q.r == N_QUEUES) {
         const uint32_t c = q.at < total ? q.at : NO_ITEM;
         q.at = NO_ITEM;
@@ -395,9 +395,7 @@ __device__ __forceinline__ uint32_t take_work(WorkQueue &q, uint32_t *counters, 
         const uint32_t n_r = queue_positions(total, q.r);
         if (q.at < q.seen && q.at < n_r) return queue_item(q.at++, q.r, total);
         if (q.seen < n_r) {
-            // (n is at most a fourth of what is left, so a counter stays far below 2^32)
-            const int share = 33 - __clz(max(1, grid_blocks * (BLOCK / WAVE) / N_QUEUES));
-            const uint32_t n = max(1u, (n_r - q.seen) >> share);
+            const uint32_t n = queue_run(n_r - q.seen, (uint32_t)grid_blocks, single);
             uint32_t v = 0;
             if (lane == 0) v = atomicAdd(counters + q.r * QUEUE_STRIDE, n);
             q.at = uniform_u32(v);
@@ -574,7 +572,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
     bool empty = true;
     #pragma unroll 1
     for (;;) {
-        const uint32_t c = take_work(wq, queue, (uint32_t)total_chunks, grid_blocks, lane);
+        const uint32_t c = take_work(wq, queue, (uint32_t)total_chunks, grid_blocks, fans_inline != 0, lane);
         if (c == NO_ITEM) break;
 
         if (c < cur_begin || c >= cur_end) {
@@ -1018,7 +1016,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SRP_WPE_F
     #pragma unroll 1
     for (;;) {
         // (the fan kernel's own counters)
-        const uint32_t c = take_work(wq, queue + N_QUEUES * QUEUE_STRIDE, total, grid_blocks, lane);
+        const uint32_t c = take_work(wq, queue + N_QUEUES * QUEUE_STRIDE, total, grid_blocks, false, lane);
         if (c == NO_ITEM) break;
         const int4 U = ((const int4 SRP_GLOBAL *)units)[c];
         if (U.x != cur) {

@@ -355,6 +355,17 @@ SRP_HD inline uint32_t queue_item(uint32_t i, uint32_t r, uint32_t total) {
     const uint32_t skew = i < total / N_QUEUES ? i * 37u : 0u;
     return i * N_QUEUES + ((r + skew) & (N_QUEUES - 1));
 }
+// The items that one request takes when a queue has `left`: about a fourth of a wave's
+// share of them (so that the 32-bit counters do not overflow), one at a time at the
+// end; one at a time throughout where an item is long beside a request (`single`: chunks that trace
+// their diffuse fans, of up to 1.7 ms; in runs, 24 images at 400^2 of the 8k craft, B = 2,
+// K = 16, took 2,196 us, so 1,924, the box-wing 454 and 463).
+SRP_HD inline uint32_t queue_run(uint32_t left, uint32_t blocks, bool single) {
+    const uint32_t waves = blocks * (BLOCK / 64) / N_QUEUES;   // of one counter
+    const int share = 33 - __builtin_clz(waves > 1u ? waves : 1u);
+    const uint32_t n = single ? 0u : left >> share;
+    return n > 1u ? n : 1u;
+}
 // Whether each of `total` items belongs to a wave of its own, and which: the waves
 // suffice, and there is a block for every compute unit.  (A smaller launch ends on the
 // compute unit that holds most of its long patches, which a queue spreads: the 36

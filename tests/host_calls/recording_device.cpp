@@ -70,6 +70,8 @@ int queue_faults(uint32_t total, uint32_t blocks) {
     return faults + (int)std::count(seen.begin(), seen.end(), 0);
 }
 
+uint32_t run_of(uint32_t left, uint32_t blocks, int single) { return queue_run(left, blocks, single != 0); }
+
 hipError_t hipMalloc(void **p, size_t n) {
     *p = nullptr;
     if (g_used + n > g_limit) return hipErrorOutOfMemory;

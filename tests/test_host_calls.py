@@ -313,3 +313,15 @@ def test_images_with_crowded_tiles_keep_the_traversal(dev, mesh, n, items, raste
     assert dev.batch([(sc, params(SUN, n, 1))] * items + [(other, params(SUN, 1024, 1))]) == 0, dev.error()
     got = [r for r in dev.log() if r[0] == "primary"]
     assert [r[2] for r in got] == [items + 1 if rasterised else 1] and dev.lib.dev_faults() == 0
+
+
+def test_long_items_are_taken_one_at_a_time(dev):
+    """Chunks that trace their own diffuse fans are long beside a request: runs of them end
+    a launch on the waves that took the last ones.  Others go in runs of at most a
+    fourth of what is left, whatever the launch."""
+    dev.lib.run_of.restype = C.c_uint32
+    for blocks in (1, 16, 256, 512, 1024):
+        for left in (1, 2, 100, 4096, 1 << 25):
+            assert dev.lib.run_of(left, blocks, 1) == 1
+            assert 1 <= dev.lib.run_of(left, blocks, 0) <= max(1, left // 4)
+    assert dev.lib.run_of(4096, 1024, 0) > 1
