@@ -573,9 +573,14 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     // 516 / 798, 596 / 829, 926 / 1115; a 5,120-triangle sphere at 256^2 1748 / 2154, 4088 / 4602,
     // 4145 / 4652, 7551 / 8080.  A separate launch costs about 4 ns per patch and a microsecond per
     // pass; inline, a launch ends on a few patches of up to 1.7 ms each, which weighs
-    // more where a launch is small and rays are expensive.
+    // more where a launch is small and rays are expensive.  Few rays per emitter from few
+    // triangles are not worth a launch: the box-wing at B x K = 4 x 4, 256^2 x 30, 247 / 334, at
+    // 2 x 8 295 / 380, at 2 x 16 421 / 482 (but 100^2 x 45 240 / 205), at 2 x 31 610 / 616; 80
+    // triangles, 256^2 x 30, at 4 x 4 521 / 665, at 2 x 8 742 / 865, at 1 x 16 1,254 / 1,187.
+    // (The line at 32,768 triangles is drawn between the 20k and 50k crafts; an 82k
+    // sphere, 256^2 x 64 at 2 x 16, still takes 7,770 / 7,940, the 8k craft 400^2 x 24 1,924 / 1,511.)
     // (A unit list numbers its passes with 32 bits: a batch of more keeps its fans inline.)
-    int64_t fan_patches = 0, fan_rays = INT64_MAX, fan_tris = INT64_MAX;
+    int64_t fan_patches = 0, fan_k = INT64_MAX, fan_rays = INT64_MAX, fan_tris = INT64_MAX;
     // partial slots: one per pass of 64 tasks (emitter, slice of FAN_SLICE fan rays), at
     // most bounces x ceil(n_diffuse / FAN_SLICE) per patch
     L.fan_base.assign(n + 1, 0);
@@ -586,6 +591,7 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         const int64_t np = L.patch_base[k + 1] - L.patch_base[k];
         L.total_fan_slots += np * p.bounces * ((p.n_diffuse + FAN_SLICE - 1) / FAN_SLICE);
         fan_patches += np;
+        fan_k = std::min<int64_t>(fan_k, p.n_diffuse);
         fan_rays = std::min<int64_t>(fan_rays, (int64_t)p.bounces * p.n_diffuse);
         fan_tris = std::min<int64_t>(fan_tris, items[k].scene->h.n_tris);
     }
@@ -593,7 +599,9 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     constexpr int64_t MAX_UNITS = (int64_t)1 << 31;
     if (fan_patches > 0) {
         const int64_t resident = (int64_t)g_ws.n_cu * fan_blocks_per_cu(L.count) * (BLOCK / 64);
-        const bool dear = roomy && L.total_fan_slots <= MAX_UNITS && fan_rays >= 16 &&
+        const bool many = fan_rays >= 16 &&
+                          (fan_tris >= 1024 || (fan_k >= 16 && (fan_tris >= 64 || fan_rays >= 48)));
+        const bool dear = roomy && L.total_fan_slots <= MAX_UNITS && many &&
                           (fan_tris >= 32768 || fan_patches < 8 * resident);
         L.fans_inline = fan_patches >= 2 * resident && !dear;
     }

@@ -325,3 +325,21 @@ def test_long_items_are_taken_one_at_a_time(dev):
             assert dev.lib.run_of(left, blocks, 1) == 1
             assert 1 <= dev.lib.run_of(left, blocks, 0) <= max(1, left // 4)
     assert dev.lib.run_of(4096, 1024, 0) > 1
+
+
+@pytest.mark.parametrize("mesh,n,items,bounces,diffuse,listed", [
+    ("box-wing", 256, 2, 4, 4, True),       # a small launch: always
+    ("box-wing", 256, 30, 4, 4, False),
+    ("box-wing", 256, 30, 2, 16, False),
+    ("box-wing", 256, 30, 2, 31, True),
+    ("80 triangles", 256, 30, 2, 8, False),
+    ("80 triangles", 256, 30, 1, 16, True),
+    ("craft", 256, 30, 2, 8, True),
+    ("craft", 256, 64, 2, 16, False),       # a big launch of cheap rays
+])
+def test_fans_of_few_rays_from_few_triangles_have_no_launch_of_their_own(dev, mesh, n, items, bounces, diffuse, listed):
+    m = {"box-wing": synth.box_wing, "80 triangles": lambda: synth.icosphere(subdiv=1),
+         "craft": lambda: synth.procedural_sized(3, 8000)}[mesh]()
+    assert dev.batch([(dev.scene(m), params(SUN, n, bounces, diffuse=diffuse))] * items) == 0, dev.error()
+    trace = [r for r in dev.log() if r[0] == "trace"]
+    assert len(trace) == 1 and trace[0][3] != trace[0][4] and trace[0][4] == listed
