@@ -840,16 +840,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
 template <bool DIR>
 __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(
     const EvalDesc *__restrict__ descs, int n_evals, const uint32_t *__restrict__ block_base, uint32_t first_block,
-    uint32_t max_blocks, int block_waves, const PatchOut *__restrict__ patches, int lds_grad_doubles) {
+    uint32_t per_most, int block_waves, const PatchOut *__restrict__ patches, int lds_grad_doubles) {
     extern __shared__ char smem[];
     const int lane = threadIdx.x & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     double *gw = reinterpret_cast<double *>(smem) + (size_t)wv * lds_grad_doubles;
     const uint32_t SRP_CONST *base = (const uint32_t SRP_CONST *)block_base;
     const uint32_t block = first_block + blockIdx.x;
-    const int e = __builtin_amdgcn_readfirstlane(block_owner(base, n_evals, block, max_blocks));
-    const EvalDesc &D = descs[e];
+    const BlockOwner own = block_owner(base, n_evals, block, per_most);
+    const EvalDesc &D = descs[own.eval];
     const int parts = D.group / GROUP_PART, part = wv % parts;   // (powers of two; parts <= block_waves)
-    const int64_t kc = ((int64_t)(block - base[e]) * block_waves + wv) / parts;
+    const int64_t kc = ((int64_t)(block - own.first) * block_waves + wv) / parts;
     const bool mine = kc < D.n_groups;
     for (int i = lane; i < D.grad_n; i += WAVE) gw[i] = 0.0;
     wave_lds_fence();
@@ -1434,10 +1434,10 @@ int launch_adjoint(const EvalDesc *d_desc, int n_evals, const uint32_t *d_block_
         const dim3 grid(std::min(n_blocks - b, MAX_LAUNCH_BLOCKS));
         if (dir)
             hipLaunchKernelGGL((k_adjoint<true>), grid, block, lds, (hipStream_t)stream, d_desc, n_evals, d_block_base,
-                               b, max_blocks, block_waves, d_patches, lds_grad_doubles);
+                               b, launch_share(max_blocks), block_waves, d_patches, lds_grad_doubles);
         else
             hipLaunchKernelGGL((k_adjoint<false>), grid, block, lds, (hipStream_t)stream, d_desc, n_evals, d_block_base,
-                               b, max_blocks, block_waves, d_patches, lds_grad_doubles);
+                               b, launch_share(max_blocks), block_waves, d_patches, lds_grad_doubles);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return (int)err;
     }

@@ -145,7 +145,7 @@ __device__ __forceinline__ bool box_meets(const PrimaryInst SRP_CONST &M, const 
 template <int TW>
 __global__ __launch_bounds__(WAVE) void k_primary(const EvalDesc *__restrict__ descs, int n_evals,
                                                   const uint32_t *__restrict__ tile_base, uint32_t first_tile,
-                                                  uint32_t max_tiles) {
+                                                  uint32_t per_most) {
     __shared__ uint64_t zb[TW * TW];   // patch-major: (patch of the tile) * 64 + pixel of the patch
     __shared__ uint32_t stk[STACK_CAP];
     __shared__ uint32_t lst[LIST_CAP];
@@ -157,11 +157,12 @@ __global__ __launch_bounds__(WAVE) void k_primary(const EvalDesc *__restrict__ d
     const int lane = threadIdx.x;
     const uint32_t SRP_CONST *base = (const uint32_t SRP_CONST *)tile_base;
     const uint32_t block = first_tile + blockIdx.x;
-    const int e = __builtin_amdgcn_readfirstlane(block_owner(base, n_evals, block, max_tiles));
+    const BlockOwner own = block_owner(base, n_evals, block, per_most);
+    const int e = own.eval;
     const EvalDesc SRP_CONST &D = ((const EvalDesc SRP_CONST *)descs)[e];
     const int N = D.n, gp = 2 * D.tiles_x;             // patches per row of the image
     const int nt = (gp + PW - 1) / PW;                 // tiles per row
-    const int tile = (int)(block - base[e]);
+    const int tile = (int)(block - own.first);
     const int tx = tile % nt, ty = tile / nt;
     const int X0 = tx * TW, Y0 = ty * TW;
     const int X1 = min(X0 + TW, N) - 1, Y1 = min(Y0 + TW, N) - 1;
@@ -357,10 +358,10 @@ int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, i
         const dim3 grid(n_tiles - b < MAX_LAUNCH_BLOCKS ? n_tiles - b : MAX_LAUNCH_BLOCKS);
         if (tile == 16)
             hipLaunchKernelGGL((k_primary<16>), grid, dim3(WAVE), 0, (hipStream_t)stream, d_desc, n_evals, d_tile_base,
-                               b, max_tiles);
+                               b, launch_share(max_tiles));
         else
             hipLaunchKernelGGL((k_primary<8>), grid, dim3(WAVE), 0, (hipStream_t)stream, d_desc, n_evals, d_tile_base,
-                               b, max_tiles);
+                               b, launch_share(max_tiles));
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return (int)err;
     }

@@ -427,20 +427,32 @@ SRP_HD inline int64_t adjoint_blocks(int64_t n_groups, int group, int block_wave
 // work-items with 32 bits).
 constexpr uint32_t MAX_LAUNCH_BLOCKS = (uint32_t)1 << 22;
 
-// The evaluation that owns block b of a launch numbered through its batch: base[k]
-// blocks before evaluation k, base[n] > b in all, at most `most` of one.  Evaluations
-// of one size need no search: none before b / most can own b.
+// The evaluation that owns block b of a launch numbered through its batch, and its first
+// block: base[k] blocks before evaluation k, base[n] > b in all.  per_most: 2^32 over the
+// most blocks of one (launch_share), so that no evaluation before b / most can own b:
+// evaluations of one size need no search (nor a division, 2 % of the rasteriser on
+// 8-pixel tiles).
+struct BlockOwner {
+    int eval;
+    uint32_t first;
+};
+inline uint32_t launch_share(uint32_t most) { return most > 1 ? (uint32_t)(((uint64_t)1 << 32) / most) : 0xFFFFFFFFu; }
 template <class P>
-SRP_HD inline int block_owner(P base, int n, uint32_t b, uint32_t most) {
-    const uint32_t first = b / most;
-    int lo = (int)(first < (uint32_t)(n - 1) ? first : (uint32_t)(n - 1));
-    if (b < base[lo + 1]) return lo;
+SRP_HD inline BlockOwner block_owner(P base, int n, uint32_t b, uint32_t per_most) {
+    int lo = (int)(((uint64_t)b * per_most) >> 32);   // b / most, or one less
+    if (lo > n - 1) lo = n - 1;
+    uint32_t first = base[lo], next = base[lo + 1];
+    if (b >= next && lo < n - 1) {
+        first = next;
+        next = base[++lo + 1];
+    }
+    if (b < next) return {lo, first};
     int hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (base[mid] <= b) lo = mid; else hi = mid - 1;
     }
-    return lo;
+    return {lo, base[lo]};
 }
 // Diffuse fans of the recorded emitters: one work unit per non-empty fan pass,
 // as the trace kernel listed them in d_fan_units (at most max_units); uses the

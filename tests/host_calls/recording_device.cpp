@@ -184,8 +184,9 @@ void check_owners(const uint32_t *base, int n, uint32_t total, uint32_t most) {
     for (int k = 0; k < n; ++k)
         if (base[k + 1] - base[k] > most) ++g_faults;
     for (uint32_t b = 0; b < total; ++b) {
-        const int e = block_owner(base, n, b, most);
-        if (e < 0 || e >= n || b < base[e] || b >= base[e + 1]) ++g_faults;
+        const BlockOwner own = block_owner(base, n, b, launch_share(most));
+        const int e = own.eval;
+        if (e < 0 || e >= n || b < base[e] || b >= base[e + 1] || own.first != base[e]) ++g_faults;
     }
 }
 // PRIMARY: evaluations, of them rasterised, tile, blocks launched
