@@ -367,6 +367,7 @@ struct Layout {
     uint32_t tile_most = 0;            // most tiles of any item
     size_t o_vis = 0, o_vmask = 0, o_tbase = 0;
     bool fans_inline = false;   // the trace kernel traces the fans itself (no fan launch)
+    bool long_chunks = false;   // and its chunks are long beside a request to the queues
     // captured forward plans of one patch per chunk: the patch order of the next
     // launch and the per-patch costs it is made from (layout_add_order)
     bool ordered = false;
@@ -604,6 +605,9 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
         const bool dear = roomy && L.total_fan_slots <= MAX_UNITS && many &&
                           (fan_tris >= 32768 || fan_patches < 8 * resident);
         L.fans_inline = fan_patches >= 2 * resident && !dear;
+        // (110 images of the box-wing at 189^2, 1 x 1, 354 us in runs of chunks, 387 one at a
+        // time; of 24 at 400^2, 4 x 4 349 / 377; the crafts' gain is at queue_run)
+        L.long_chunks = L.fans_inline && fan_rays >= 8 && fan_tris >= 1024;
     }
     // the fan launch's unit list: room for every pass slot (each patch lists at
     // most its slots)
@@ -1032,8 +1036,8 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
     };
     if (L.windows.empty()) {
         e = launch_trace(d_desc, d_cbase, (int)L.n, d_win, L.total_chunks, d_queue, d_spill, d_patches, d_counts,
-                         L.count, L.grid, d_fan_out, d_fan_counts, L.fans_inline, d_units, L.sch.bpc, d_order, d_cost,
-                         stream);
+                         L.count, L.grid, d_fan_out, d_fan_counts, L.fans_inline, L.long_chunks, d_units, L.sch.bpc, d_order,
+                         d_cost, stream);
         if (e) return trace_failed(e);
     }
     if (L.total_units > 0) {
@@ -1056,7 +1060,7 @@ int enqueue(const Layout &L, char *Dv, const char *H, size_t copy_bytes, const B
         if (e) return fail(SRP_ERR_DEVICE, std::string("window kernel: ") + hipGetErrorString((hipError_t)e));
         e = launch_trace(d_pieces, reinterpret_cast<const int64_t *>(Dv + L.o_pcbase) + at, (int)W.count, d_pwin,
                          W.chunks, d_queue, d_spill, d_patches, d_counts, L.count, L.grid, nullptr, nullptr, false,
-                         nullptr, L.sch.bpc, nullptr, nullptr, stream);
+                         false, nullptr, L.sch.bpc, nullptr, nullptr, stream);
         if (e) return trace_failed(e);
         e = launch_adjoint(d_pieces, (int)W.count, reinterpret_cast<const uint32_t *>(Dv + L.o_pabase) + at, W.blocks,
                            W.most, L.adj_waves, d_patches, L.dir, L.max_grad_n, stream);
@@ -1253,7 +1257,7 @@ int plan_refill(PlanImpl *P, const srp_batch_item *items, int64_t n, bool *compa
         L2.grad_n != L.grad_n || L2.chain_off != L.chain_off || L2.pieces != L.pieces || L2.chunk_base != L.chunk_base ||
         L2.patch_base != L.patch_base || L2.o_patches != L.o_patches || L2.o_counts != L.o_counts ||
         L2.total_units != L.total_units || L2.fan_base != L.fan_base || L2.fan_grid != L.fan_grid ||
-        L2.o_units != L.o_units || L2.fans_inline != L.fans_inline ||
+        L2.o_units != L.o_units || L2.fans_inline != L.fans_inline || L2.long_chunks != L.long_chunks ||
         L2.emit_off != L.emit_off ||
         L2.o_emask != L.o_emask || L2.o_fanout != L.o_fanout || L2.o_fancnt != L.o_fancnt ||
         L2.o_queue != L.o_queue || L2.o_spill != L.o_spill || L2.slots.size() != L.slots.size() ||

@@ -572,7 +572,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE ? WPE
     bool empty = true;
     #pragma unroll 1
     for (;;) {
-        const uint32_t c = take_work(wq, queue, (uint32_t)total_chunks, grid_blocks, fans_inline != 0, lane);
+        const uint32_t c = take_work(wq, queue, (uint32_t)total_chunks, grid_blocks, fans_inline == 2, lane);
         if (c == NO_ITEM) break;
 
         if (c < cur_begin || c >= cur_end) {
@@ -1402,11 +1402,11 @@ size_t trace_lds_bytes() { return sizeof(uint32_t) * STACK_LDS * BLOCK + sizeof(
 int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_evals, const uint64_t *d_win,
                  int64_t total_chunks, uint32_t *d_queue, uint32_t *d_spill, PatchOut *d_chunks,
                  uint64_t *d_counts, bool count, int grid_blocks, PatchOut *d_fan_out, uint64_t *d_fan_counts,
-                 bool fans_inline_, int4 *d_fan_units, int blocks_per_cu, const uint32_t *d_order, uint32_t *d_cost,
+                 bool fans_inline_, bool long_chunks, int4 *d_fan_units, int blocks_per_cu, const uint32_t *d_order, uint32_t *d_cost,
                  void *stream) {
     if (total_chunks <= 0) return 0;
     const size_t lds = trace_lds_bytes();
-    const int fans_inline = (d_fan_out && fans_inline_) ? 1 : 0;
+    const int fans_inline = (d_fan_out && fans_inline_) ? (long_chunks ? 2 : 1) : 0;
     int4 *fan_units = (d_fan_out && !fans_inline_) ? d_fan_units : nullptr;
     hipStream_t s = (hipStream_t)stream;
 #define SRP_LAUNCH_TRACE(C, W)                                                                                    \

@@ -357,9 +357,9 @@ SRP_HD inline uint32_t queue_item(uint32_t i, uint32_t r, uint32_t total) {
 }
 // The items that one request takes when a queue has `left`: about a fourth of a wave's
 // share of them (so that the 32-bit counters do not overflow), one at a time at the
-// end; one at a time throughout where an item is long beside a request (`single`: chunks that trace
-// their diffuse fans, of up to 1.7 ms; in runs, 24 images at 400^2 of the 8k craft, B = 2,
-// K = 16, took 2,196 us, so 1,924, the box-wing 454 and 463).
+// end; one at a time throughout where an item is long beside a request (`single`: chunks
+// that trace the diffuse fans of a craft, of up to 1.7 ms; in runs, 24 images at 400^2 of the
+// 8k craft, B = 2, K = 16, took 2,196 us, so 1,924).
 SRP_HD inline uint32_t queue_run(uint32_t left, uint32_t blocks, bool single) {
     const uint32_t waves = blocks * (BLOCK / 64) / N_QUEUES;   // of one counter
     const int share = 33 - __builtin_clz(waves > 1u ? waves : 1u);
@@ -398,7 +398,8 @@ int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, i
 // d_spill: grid_blocks * BLOCK * STACK_SPILL words; chunk counts below 2^31.
 // d_fan_out, d_fan_counts (forward, diffuse rays on): the fan pass partial
 // slots.  With fans_inline the trace kernel also traces every patch's diffuse
-// fans into them (no fan launch follows); otherwise it lists each patch's
+// fans into them (no fan launch follows; long_chunks: its waves take one chunk at
+// a time, queue_run); otherwise it lists each patch's
 // non-empty passes in d_fan_units (capacity: one entry per pass slot; their
 // number at d_queue[FAN_UNITS_AT]) for the fan launch and writes the empty
 // passes' zero partials itself.  blocks_per_cu <= 2 (grid_blocks = that times the CU count) launches the
@@ -410,7 +411,7 @@ int launch_primary(const EvalDesc *d_desc, int n_evals, const uint64_t *d_win, i
 int launch_trace(const EvalDesc *d_desc, const int64_t *d_chunk_base, int n_evals,
                  const uint64_t *d_win, int64_t total_chunks, uint32_t *d_queue, uint32_t *d_spill,
                  PatchOut *d_patches, uint64_t *d_counts, bool count, int grid_blocks, PatchOut *d_fan_out,
-                 uint64_t *d_fan_counts, bool fans_inline, int4 *d_fan_units, int blocks_per_cu,
+                 uint64_t *d_fan_counts, bool fans_inline, bool long_chunks, int4 *d_fan_units, int blocks_per_cu,
                  const uint32_t *d_order, uint32_t *d_cost, void *stream);
 // Gradient partials of every group from the chains and hit counts that the
 // trace kernel wrote, in blocks of block_waves = max group / GROUP_PART waves.

@@ -225,10 +225,10 @@ int64_t patches_of(const EvalDesc *d, int n) {
     for (int k = 0; k < n; ++k) np += d[k].n_patches - d[k].patch0;
     return np;
 }
-// TRACE: evaluations, chunks, fans traced inside, fan units listed
+// TRACE: evaluations, chunks, fans traced inside, fan units listed, chunks taken one at a time
 int launch_trace(const EvalDesc *d, const int64_t *chunk_base, int n_evals, const uint64_t *, int64_t total_chunks,
                  uint32_t *, uint32_t *, PatchOut *patches, uint64_t *, bool, int, PatchOut *d_fan_out, uint64_t *,
-                 bool fans_inline, int4 *d_fan_units, int, const uint32_t *, uint32_t *, void *) {
+                 bool fans_inline, bool long_chunks, int4 *d_fan_units, int, const uint32_t *, uint32_t *, void *) {
     int64_t at = 0;
     for (int k = 0; k < n_evals; ++k) {
         if (chunk_base[k] != at) ++g_faults;
@@ -243,7 +243,7 @@ int launch_trace(const EvalDesc *d, const int64_t *chunk_base, int n_evals, cons
                 c[0] = c[64 * (d[k].bounces + 1) - 1] = (uint32_t)(d[k].patch_base + pt) + 1u;
                 std::memset((void *)&patches[d[k].patch_base + pt], 0xEE, sizeof(PatchOut));
             }
-    note(TRACE, n_evals, total_chunks, d_fan_out && fans_inline, d_fan_units != nullptr);
+    note(TRACE, n_evals, total_chunks, d_fan_out && fans_inline, d_fan_units != nullptr, long_chunks);
     return 0;
 }
 // ADJOINT: evaluations, blocks launched, waves per block; every group in a block of its own evaluation

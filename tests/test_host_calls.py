@@ -316,9 +316,13 @@ def test_images_with_crowded_tiles_keep_the_traversal(dev, mesh, n, items, raste
 
 
 def test_long_items_are_taken_one_at_a_time(dev):
-    """Chunks that trace their own diffuse fans are long beside a request: runs of them end
+    """Chunks that trace a craft's diffuse fans are long beside a request: runs of them end
     a launch on the waves that took the last ones.  Others go in runs of at most a
     fourth of what is left, whatever the launch."""
+    craft, small = dev.scene(synth.procedural_sized(3, 8000)), dev.scene(synth.box_wing())
+    for sc, diffuse, single in ((craft, 16, 1), (craft, 1, 0), (small, 1, 0), (small, 16, 0), (craft, 0, 0)):
+        assert dev.batch([(sc, params(SUN, 400, 1, diffuse=diffuse))] * 24) == 0, dev.error()
+        assert [r[5] for r in dev.log() if r[0] == "trace"] == [single]
     dev.lib.run_of.restype = C.c_uint32
     for blocks in (1, 16, 256, 512, 1024):
         for left in (1, 2, 100, 4096, 1 << 25):
