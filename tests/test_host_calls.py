@@ -293,7 +293,12 @@ def _on_booms(subdiv, length):
     ("crowded", 512, 32, False),     # 81,920 triangles on a few tiles, 0.31 per pixel of the whole image
     ("crowded", 1024, 64, True),     # the same body over some dozen tiles of a launch of a million patches
     ("crowded", 2048, 1, True),      # and over more of them in one fine image
+    ("crowded", 1024, 8, True),
+    ("crowded", 1040, 8, True),
     ("even", 512, 64, True),         # as many triangles all over the image
+    ("even", 400, 53, True),         # 0.51 per pixel: only in launches of 131,072 patches
+    ("even", 372, 60, True),
+    ("even", 368, 62, False),        # 0.605
     ("craft", 300, 648, True),
     ("craft", 1024, 64, True),
     ("craft", 512, 8, True),
@@ -347,3 +352,18 @@ def test_fans_of_few_rays_from_few_triangles_have_no_launch_of_their_own(dev, me
     assert dev.batch([(dev.scene(m), params(SUN, n, bounces, diffuse=diffuse))] * items) == 0, dev.error()
     trace = [r for r in dev.log() if r[0] == "trace"]
     assert len(trace) == 1 and trace[0][3] != trace[0][4] and trace[0][4] == listed
+
+
+def test_rasterised_hits_in_the_fixed_workspace_and_across_the_cap(dev):
+    """The hits of 16 images at 256^2 fit beside the whole grid's stacks in the fixed
+    workspace, those of 30 at 512^2 do not and are left out; a batch whose hits pass
+    the workspace cap runs as rasterised sub-batches.  (And 130,000 patches at 0.51
+    triangles per pixel are too few.)"""
+    dense = dev.scene(synth.icosphere(subdiv=6))
+    assert dev.batch([(dense, params(SUN, 400, 1))] * 52) == 0 and not [r for r in dev.log() if r[0] == "primary"]
+    sc = dev.scene(synth.procedural_sized(7, 4000))
+    for n, items, rasterised in ((256, 16, [16]), (512, 30, [])):
+        assert dev.batch([(sc, params(SUN, n, 2))] * items, noalloc=True) == 0, dev.error()
+        assert [r[2] for r in dev.log() if r[0] == "primary"] == rasterised
+    assert dev.batch([(sc, params(SUN, 8192, 0))] * 30) == 0, dev.error()
+    assert [r[2] for r in dev.log() if r[0] == "primary"] == [15, 15]
