@@ -899,90 +899,90 @@ __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(
             for (int i = 0; i < 3; ++i) d[i] = fmaf(2.0f * cth, last.n[i], d[i]);
             w *= last.rs;
         }
-            // Reverse sweep over the chain at fixed visibility.
-            //   A  = d(sum of later contributions)/d(incoming direction)   (3x3)
-            //   Tn = later contributions divided by the weight after this hit
-            float A[9], Tn[3] = {0, 0, 0};
-            float n0[3] = {0, 0, 0}, c0 = 1.0f;   // the primary hit's normal and cosine (DIR)
-            m3_zero(A);
-            for (int k = Kmax - 1; k >= 0; --k) {
-                const bool act = k < K;
-                float Hm[9], gmat[6];
-                int node = 0, mat = 0;
-                if (act) {
-                    // hit k's normal exactly as the forward pass computed it
-                    ChainHit C = last;
-                    if (k < K - 1) C = chain_hit(TC, D, cw.at(chain, k));
-                    const int tnode = C.node, tmat = C.mat;
-                    const float n[3] = {C.n[0], C.n[1], C.n[2]}, rs = C.rs, rd = C.rd;
-                    // (d, w) hold the ray after hit k when hit k spawned one: undo the
-                    // reflection and the weight factor to get hit k's incoming ray
-                    if (k < K - 1 || cont) {
-                        const float dn = n[0] * d[0] + n[1] * d[1] + n[2] * d[2];
-                        for (int i = 0; i < 3; ++i) d[i] = fmaf(-2.0f * dn, n[i], d[i]);
-                        w = w / rs;
-                    }
-                    const float cc = -(n[0] * d[0] + n[1] * d[1] + n[2] * d[2]);
-                    const float sc = rs * cc + rd * (1.0f / 3.0f);
-                    if (DIR && k == 0) {
-                        for (int i = 0; i < 3; ++i) n0[i] = n[i];
-                        c0 = cc;
-                    }
-                    // material terms
-                    for (int i = 0; i < 3; ++i) {
-                        gmat[i] = w * (-d[i] - 2.0f * cc * n[i] + Tn[i]);
-                        gmat[3 + i] = w * (-2.0f / 3.0f) * n[i];
-                    }
-                    // G = dF/dn (explicit) + A (2c I - 2 n d^T)
-                    float G[9];
-                    for (int i = 0; i < 3; ++i)
-                        for (int j = 0; j < 3; ++j) {
-                            float e = w * (2.0f * rs * n[i] * d[j] - (i == j ? 2.0f * sc : 0.0f));
-                            float an = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
-                            e += 2.0f * cc * A[3 * i + j] - 2.0f * an * d[j];
-                            G[3 * i + j] = e;
-                        }
-                    if (k == 0) {
-                        // the primary ray keeps its share of the triangle's visible surface,
-                        // whose projected area scales with c0 = -n0.d: the whole chain's
-                        // contribution S (per unit weight) adds dF/dn0 = -S d^T / c0
-                        float S[3];
-                        for (int i = 0; i < 3; ++i) S[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
-                        const float ws = w / cc;
-                        for (int i = 0; i < 3; ++i)
-                            for (int j = 0; j < 3; ++j) G[3 * i + j] -= ws * S[i] * d[j];
-                    }
-                    // H = -G [n]x
-                    for (int i = 0; i < 3; ++i) {
-                        const float g0 = G[3 * i], g1 = G[3 * i + 1], g2 = G[3 * i + 2];
-                        Hm[3 * i + 0] = -(g1 * n[2] - g2 * n[1]);
-                        Hm[3 * i + 1] = -(g2 * n[0] - g0 * n[2]);
-                        Hm[3 * i + 2] = -(g0 * n[1] - g1 * n[0]);
-                    }
-                    // A <- dF_k/dd + A (I - 2 n n^T);  Tn <- f_k + rs Tn
-                    float An[3];
-                    for (int i = 0; i < 3; ++i) An[i] = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
-                    for (int i = 0; i < 3; ++i)
-                        for (int j = 0; j < 3; ++j)
-                            A[3 * i + j] = A[3 * i + j] - 2.0f * An[i] * n[j] +
-                                           w * ((i == j ? 1.0f - rs : 0.0f) + 2.0f * rs * n[i] * n[j]);
-                    for (int i = 0; i < 3; ++i) Tn[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
-                    node = tnode;
-                    mat = tmat;
+        // Reverse sweep over the chain at fixed visibility.
+        //   A  = d(sum of later contributions)/d(incoming direction)   (3x3)
+        //   Tn = later contributions divided by the weight after this hit
+        float A[9], Tn[3] = {0, 0, 0};
+        float n0[3] = {0, 0, 0}, c0 = 1.0f;   // the primary hit's normal and cosine (DIR)
+        m3_zero(A);
+        for (int k = Kmax - 1; k >= 0; --k) {
+            const bool act = k < K;
+            float Hm[9], gmat[6];
+            int node = 0, mat = 0;
+            if (act) {
+                // hit k's normal exactly as the forward pass computed it
+                ChainHit C = last;
+                if (k < K - 1) C = chain_hit(TC, D, cw.at(chain, k));
+                const int tnode = C.node, tmat = C.mat;
+                const float n[3] = {C.n[0], C.n[1], C.n[2]}, rs = C.rs, rd = C.rd;
+                // (d, w) hold the ray after hit k when hit k spawned one: undo the
+                // reflection and the weight factor to get hit k's incoming ray
+                if (k < K - 1 || cont) {
+                    const float dn = n[0] * d[0] + n[1] * d[1] + n[2] * d[2];
+                    for (int i = 0; i < 3; ++i) d[i] = fmaf(-2.0f * dn, n[i], d[i]);
+                    w = w / rs;
                 }
-                wave_scatter_add<9>(gw, node, act, Hm, 9);
-                wave_scatter_add<6>(gw + 9 * gK, mat, act, gmat, 6);
-            }
-            // Photon-direction Jacobian of the ray's whole chain, each primary ray
-            // keeping its triangle and its share of that triangle's visible area
-            // (the share's projected area scales with c = -n0.d):
-            //   dF/dd = A - S n0^T / c0,  S = chain contribution per unit weight (Tn)
-            if (DIR && (D.flags & SRP_F_GRAD_DIR)) {
-                float Jd[9];
+                const float cc = -(n[0] * d[0] + n[1] * d[1] + n[2] * d[2]);
+                const float sc = rs * cc + rd * (1.0f / 3.0f);
+                if (DIR && k == 0) {
+                    for (int i = 0; i < 3; ++i) n0[i] = n[i];
+                    c0 = cc;
+                }
+                // material terms
+                for (int i = 0; i < 3; ++i) {
+                    gmat[i] = w * (-d[i] - 2.0f * cc * n[i] + Tn[i]);
+                    gmat[3 + i] = w * (-2.0f / 3.0f) * n[i];
+                }
+                // G = dF/dn (explicit) + A (2c I - 2 n d^T)
+                float G[9];
                 for (int i = 0; i < 3; ++i)
-                    for (int j = 0; j < 3; ++j) Jd[3 * i + j] = A[3 * i + j] - Tn[i] * n0[j] / c0;
-                wave_scatter_add<9>(gw + 9 * gK + 6 * D.n_mats, 0, K > 0, Jd, 9);
+                    for (int j = 0; j < 3; ++j) {
+                        float e = w * (2.0f * rs * n[i] * d[j] - (i == j ? 2.0f * sc : 0.0f));
+                        float an = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
+                        e += 2.0f * cc * A[3 * i + j] - 2.0f * an * d[j];
+                        G[3 * i + j] = e;
+                    }
+                if (k == 0) {
+                    // the primary ray keeps its share of the triangle's visible surface,
+                    // whose projected area scales with c0 = -n0.d: the whole chain's
+                    // contribution S (per unit weight) adds dF/dn0 = -S d^T / c0
+                    float S[3];
+                    for (int i = 0; i < 3; ++i) S[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
+                    const float ws = w / cc;
+                    for (int i = 0; i < 3; ++i)
+                        for (int j = 0; j < 3; ++j) G[3 * i + j] -= ws * S[i] * d[j];
+                }
+                // H = -G [n]x
+                for (int i = 0; i < 3; ++i) {
+                    const float g0 = G[3 * i], g1 = G[3 * i + 1], g2 = G[3 * i + 2];
+                    Hm[3 * i + 0] = -(g1 * n[2] - g2 * n[1]);
+                    Hm[3 * i + 1] = -(g2 * n[0] - g0 * n[2]);
+                    Hm[3 * i + 2] = -(g0 * n[1] - g1 * n[0]);
+                }
+                // A <- dF_k/dd + A (I - 2 n n^T);  Tn <- f_k + rs Tn
+                float An[3];
+                for (int i = 0; i < 3; ++i) An[i] = A[3 * i] * n[0] + A[3 * i + 1] * n[1] + A[3 * i + 2] * n[2];
+                for (int i = 0; i < 3; ++i)
+                    for (int j = 0; j < 3; ++j)
+                        A[3 * i + j] = A[3 * i + j] - 2.0f * An[i] * n[j] +
+                                       w * ((i == j ? 1.0f - rs : 0.0f) + 2.0f * rs * n[i] * n[j]);
+                for (int i = 0; i < 3; ++i) Tn[i] = (1.0f - rs) * d[i] - 2.0f * sc * n[i] + rs * Tn[i];
+                node = tnode;
+                mat = tmat;
             }
+            wave_scatter_add<9>(gw, node, act, Hm, 9);
+            wave_scatter_add<6>(gw + 9 * gK, mat, act, gmat, 6);
+        }
+        // Photon-direction Jacobian of the ray's whole chain, each primary ray
+        // keeping its triangle and its share of that triangle's visible area
+        // (the share's projected area scales with c = -n0.d):
+        //   dF/dd = A - S n0^T / c0,  S = chain contribution per unit weight (Tn)
+        if (DIR && (D.flags & SRP_F_GRAD_DIR)) {
+            float Jd[9];
+            for (int i = 0; i < 3; ++i)
+                for (int j = 0; j < 3; ++j) Jd[3 * i + j] = A[3 * i + j] - Tn[i] * n0[j] / c0;
+            wave_scatter_add<9>(gw + 9 * gK + 6 * D.n_mats, 0, K > 0, Jd, 9);
+        }
     }
     if (parts > 1) __syncthreads();   // (the same for the whole block)
     else wave_lds_fence();
@@ -994,6 +994,7 @@ __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(
         dst[i] = t;
     }
 }
+
 // Fan work of the trace kernel's recorded emitters as a separate launch, for
 // batches too small to fill the GPU with whole patches: one unit per
 // non-empty fan pass, as the trace kernel listed them (evaluation, patch,
