@@ -487,16 +487,17 @@ int srp_propagate_nplate_rk78(const srp_plate *plates, int32_t n_plates, const s
                               int64_t max_rows, int64_t *n_rows);
 
 /* Measurement hook (not part of an evaluation): srp_profile(1) starts timing
- * every launch's ray-tracing kernels (the trace kernel, then the diffuse fan
- * kernel when n_diffuse > 0) with a pair of HIP events recorded on the launch
- * stream, srp_profile(0) stops; both reset the totals.  srp_profile_read waits
+ * every launch's ray kernels (the rasteriser of the primary hits where it runs,
+ * the trace kernel, then the diffuse fan kernel when n_diffuse > 0 or the
+ * adjoint kernel of a gradient launch) with a pair of HIP events recorded on the
+ * launch stream, srp_profile(0) stops; both reset the totals.  srp_profile_read waits
  * for the recorded launches and returns the summed kernel time (ms) and the
  * launch count since the last reset. */
 int srp_profile(int enable);
 int srp_profile_read(double *trace_ms, int64_t *launches);
 /* The same timing for each whole launch: HIP events on the launch stream
- * around its staging upload, articulation, window, trace, fan, reduction
- * kernels and result copy.  Returns the summed milliseconds and the launch
+ * around its staging upload, articulation, window, primary hits, trace, fan,
+ * adjoint and reduction kernels and result copy.  Returns the summed milliseconds and the launch
  * count since the last reset (a host that cannot keep the device fed shows
  * as wall time above this sum).  SRP_ERR_ARG for a null output. */
 int srp_profile_read_launch(double *launch_ms, int64_t *launches);

@@ -343,7 +343,7 @@ struct Layout {
     std::vector<int> n_slices;    // reduction range sums per item (first stage)
     std::vector<int64_t> slice_base;   // first range sum of every item, then the total
     std::vector<size_t> emit_off;   // emitter records of each item with diffuse fans (0: none)
-    std::vector<int> grad_n;   // gradient partial doubles per chunk of each item (allocation and kernel)
+    std::vector<int> grad_n;   // gradient partial doubles per gradient group of each item (allocation and kernel)
     std::vector<int> group;      // adjoint: patches per gradient group of each item
     std::vector<int64_t> n_groups;
     int adj_waves = 1;           // waves per block of the adjoint kernel
@@ -374,7 +374,7 @@ struct Layout {
     size_t o_order = 0, o_cost = 0;
 };
 
-// Gradient partial slots per chunk: 9 per node (rotation sensitivities), 6
+// Gradient partial slots per gradient group: 9 per node (rotation sensitivities), 6
 // per material, and 9 for the photon-direction Jacobian when the item asks
 // for it (SRP_F_GRAD_DIR).
 int grad_slots(const srp_scene *sc, uint32_t flags) {
@@ -415,7 +415,7 @@ int check_items(const srp_batch_item *items, int64_t n, bool grad, const BatchOu
 // runs as consecutive sub-batches.
 constexpr int GRAD_GROUP_MIN = GROUP_PART;
 constexpr size_t GRAD_PART_EVAL = (size_t)8 << 20;
-constexpr size_t WORKSPACE_CAP = (size_t)16 << 30;   // of the MI355X's 288 GB: the 32,768-evaluation table at 512^2 (8.6 GB of patch partials) runs as one launch
+constexpr size_t WORKSPACE_CAP = (size_t)16 << 30;   // of the MI355X's 288 GB: the 32,768-evaluation table at 512^2 (8.6 GB of patch partials, 70 GB of hits) runs as 8 launches
 
 int grad_group(int64_t n_patches, int grad_n) {
     int g = GRAD_GROUP_MIN;
@@ -451,17 +451,21 @@ Schedule pick_schedule(const srp_batch_item *items, int64_t n, bool grad, int64_
 }
 
 // Primary hits by rasterisation (k_primary) instead of the trace kernel's
-// traversal; both find the same hits.  Measured whole launches at B = 1, traversal
-// against rasterisation, in us: 200k triangles at 800^2 (0.31 triangles per
-// pixel, 6 evaluations) 637 / 547, 300k of the 65-node craft (0.47) 370 / 395, 20k
-// at 300^2 (0.22, 46 evaluations) 493 / 414, 200k at 300^2 (2.2) 742 / 890, at 64^2
-// (49) 1058 / 3207: a tile tests every triangle it meets, a ray only a few.  A
-// launch of few patches (one evaluation) waits for its slowest tile, then for its
-// slowest patch: 20k at 300^2, 2 evaluations 172 / 162, but one evaluation of the
-// 50k craft at 512^2, whose captured launch starts its slowest patches first, 120 /
-// 139, at 900^2 even.  The 16 triangles of the box-wing gain nothing (205 / 210).
-// Launches that fill the chip with 16-pixel tiles gain up to more triangles per
-// pixel: 648 directions of the 50k craft at 300^2 (0.55) 3,186 / 2,643.
+// traversal; both find the same hits.  A tile tests every triangle it meets, a ray
+// only a few, so what decides is the triangles per pixel, and the tiles that fill the
+// chip.  Measured whole calls at B = 1 (triangles per pixel), us, traversal / 8-pixel /
+// 16-pixel tiles, the route taken first:
+//   8-pixel: 50k craft 512^2 x 8 (0.19) 399 / 312 / 347; 8k craft 200^2 x 64 (0.20) 323 / 282 / 290;
+//   1,280-triangle sphere 128^2 x 256 (0.08) 725 / 520 / 477
+//   16-pixel: 50k craft 300^2 x 648 (0.55) 2,842 / 2,835 / 2,438; 200k craft 800^2 x 64 (0.31) 2,470 /
+//   2,263 / 1,963; 82k sphere 400^2 x 53 (0.51) 2,564 / 1,479 / 1,327
+//   traversal: 50k craft 300^2 x 46 (0.55) 512 / 470 / 518, 256^2 x 648 (0.76) 2,155 / 3,067 / 2,480;
+//   200k craft 500^2 x 64 (0.80) 1,489 / 1,444 / 1,819
+// The limits follow the crafts.  They give away what spheres would gain (1,280 triangles
+// 64^2 x 1024 (0.31) 916 / 631 / 580, 64^2 x 64 144 / 107 / 113; 82k 320^2 x 100 (0.80) 3,213 / 1,843 /
+// 1,662, 512^2 x 8 (0.31) 966 / 555 / 534), what a few fine images would (50k craft 900^2 x 1 318 /
+// 261 / 269) and 15 % of the small crafts' (2k 128^2 x 256 (0.12) 348 / 397 / 349).  The 16
+// triangles of the box-wing gain nothing (205 / 210).
 // A craft of many surfaces one behind the other costs all of them where a ray stops at
 // the first: 200 plates of 128 triangles (48 layers on average), 512^2 x 64, 2,350 / 8,500;
 // 1,000 of 8, 3,300 / 41,900; the crafts here have 1 to 3 layers.  (At about 0.2 ns per
@@ -474,8 +478,8 @@ bool use_raster(const srp_batch_item &it, double tris_per_pixel) {
 constexpr int64_t RASTER_MIN_PATCHES = 16384, RASTER_BIG_PATCHES = 131072;
 
 // The rasteriser's tile: smaller ones shorten the slowest tile of a small launch
-// (512^2 x 8 evaluations of 20k triangles: 1,287 us with 8 pixels, 1,304 with 16, 1,374
-// with 32), larger ones repeat less work (1024^2 x 64 of 50k: 3.07, 2.57 and 3.6 ms).
+// (512^2 x 8 of 50k triangles: 312 us with 8 pixels, 347 with 16), larger ones repeat less
+// work (1024^2 x 64 of 50k: 3.07, 2.57 and 3.6 ms with 8, 16 and 32).
 int raster_tile(int64_t patches) { return patches >= RASTER_BIG_PATCHES ? 16 : 8; }
 
 // A tile is one wave's, which tests its triangles at about 50 ns each, and the launch waits
@@ -744,7 +748,7 @@ int layout_build(const srp_batch_item *items, int64_t n, bool grad, Schedule for
     size_t off = L.o_slots;
     for (auto &sl : L.slots) { sl.off = off; off = align_up(off + sl.L.bytes); }
     // ... | fan pass partials | their counts | emitter records (per item) |
-    // gradient partials (per chunk)
+    // the adjoint's chains and gradient partials (per gradient group)
     L.o_patches = align_up(off);
     L.o_counts = align_up(L.o_patches + sizeof(PatchOut) * L.total_patches);
     L.o_emask = align_up(L.o_counts + (L.count ? sizeof(uint64_t) * 2 * L.total_patches : 0));
@@ -923,7 +927,7 @@ void staging_fill(const Layout &L, const srp_batch_item *items, const BatchOut &
         D.emit = fans ? reinterpret_cast<FanRec *>(Dv + L.emit_off[k]) : nullptr;
         D.emit_mask = fans ? reinterpret_cast<uint64_t *>(Dv + L.o_emask) + SRP_MAX_BOUNCES * D.patch_base : nullptr;
         D.fan_base = L.fan_base[k];
-        D.grad_n = L.grad ? L.grad_n[k] : 0;   // the per-chunk size the partials were allocated with
+        D.grad_n = L.grad ? L.grad_n[k] : 0;   // the size per group that the partials were allocated with
         D.grad_part = L.grad ? reinterpret_cast<double *>(Dv + L.gpart_off[k]) : nullptr;
         D.n_slices = L.n_slices[k];
         D.slice_base = L.slice_base[k];

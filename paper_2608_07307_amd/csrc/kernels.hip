@@ -6,7 +6,8 @@
 //             order-preserving 64-bit atomic min.
 //   k_trace   persistent: every wave takes chunks (runs of 8x8-pixel patches
 //             of one evaluation) from 64 work queues until none is left,
-//             with no block barrier; one ray per lane; primary hits of large
+//             (or, in a launch of few chunks, its own one) with no block
+//             barrier; one ray per lane; primary hits of large
 //             images read from k_primary's records; two-level traversal (top level over
 //             the kinematic-tree nodes, rigid instance transform, bottom level
 //             in rest-pose coordinates) with a per-lane stack (LDS ring, global
@@ -996,11 +997,11 @@ __global__ __launch_bounds__(WAVE * (MAX_PPC / GROUP_PART)) void k_adjoint(
 }
 
 // Fan work of the trace kernel's recorded emitters as a separate launch, for
-// batches too small to fill the GPU with whole patches: one unit per
-// non-empty fan pass, as the trace kernel listed them (evaluation, patch,
-// pass), so that one heavy patch's passes run side by side on as many waves
-// and no wave claims an empty pass.  Persistent waves and work queues as in
-// k_trace.
+// batches too small to fill the GPU with whole patches and for many fan rays through
+// large meshes (the rule is in the host code's layout): one unit per non-empty fan
+// pass, as the trace kernel listed them (evaluation, patch, pass), so that one heavy
+// patch's passes run side by side on as many waves and no wave claims an empty pass.
+// Persistent waves and work queues as in k_trace.
 template <bool COUNT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SRP_WPE_FWD))) void k_fans(
     const EvalDesc *__restrict__ descs, const uint64_t *__restrict__ win, int grid_blocks,
@@ -1102,12 +1103,12 @@ constexpr uint32_t ORDER_EVERY = 8;   // launches of a plan per rebuild of its p
 // ranges of evaluation e's patch partials (patches np q / Q .. np (q + 1) / Q),
 // then the same range of its fan pass slots, with per-thread strided sums,
 // wave butterflies and the waves in order; with GRAD also the q-th range of its
-// per-chunk gradient partials (the range split again into P contiguous slices,
-// P threads per component when the components fit the block several times,
-// each summed with eight interleaved accumulators, the slices added in order).
-// Q depends only on the evaluation's own size, so every result depends only on
-// the evaluation (and, for gradients, on the patches per chunk), not on the
-// batch around it.
+// gradient partials, one per gradient group (the range split again into P
+// contiguous slices, P threads per component when the components fit the block
+// several times, each summed with eight interleaved accumulators, the slices
+// added in order).  Q and the groups depend only on the evaluation's own size, so
+// every result depends only on the evaluation, not on the schedule or the batch
+// around it.
 template <bool COUNT, bool GRAD>
 __device__ __forceinline__ void slice_sum_block(const EvalDesc &D, int q, const PatchOut *__restrict__ patches,
                                                 const uint64_t *__restrict__ counts,

@@ -16,7 +16,7 @@
 // own traversal would find, and starts at the shading of the first hit.  (A ray
 // that lies in a triangle's plane to FP32 rounding has no meaningful distance
 // to it; a window so thin that its pixels are below that rounding, a body seen
-// edge-on, is left to the traversal.)
+// edge-on, is left to the traversal, and so is a tile of very many layers.)
 #include <float.h>
 
 #include "srp.h"
@@ -42,8 +42,8 @@ static_assert(STACK_CAP > STACK_SLACK + 4 * NODES_PER_STEP, "the stack holds a f
 // wide beside a sphere, 512^2 x 64 1,261 / 1,673 / 1,233, 1024^2 x 64 4,038 / 3,674 / 2,871; 50
 // plates three tenths wide, 1024^2 x 64 4,289 / 3,469 / 3,667.  With 16 layers the first two
 // are 1,201 and 2,852, but eight 2048^2 images of a million triangles 1,356 in place of
-// 1,284; 8 layers cost the 50k craft 5 to 12 %.  Counting the
-// hits takes 15 of 837 us over 64 x 1024^2.)
+// 1,284; 8 layers cost the 50k craft 5 to 12 %.  Counting the hits takes 15 of 837 us
+// over 64 x 1024^2.)
 constexpr int MAX_LAYERS = 24;
 
 __device__ __forceinline__ int rank_below(uint64_t m, int lane) {
