@@ -51,11 +51,12 @@ def source_digest(paths):
 
 
 def measured_traffic(schedule):
-    """HBM bytes per launch of the adjoint trace kernel from the committed
-    FETCH_SIZE / WRITE_SIZE counter runs, or None when the kernel sources have
-    changed since those counters were taken or this run's schedule (patches per
-    chunk, blocks per CU: the gradient partials are per chunk) is not the one
-    they were taken with."""
+    """HBM bytes per gradient launch (its rasteriser, trace and adjoint kernels
+    together) from the committed FETCH_SIZE / WRITE_SIZE counter runs, or None
+    when the kernel sources have changed since those counters were taken or
+    this run's schedule (patches per chunk, blocks per CU: they set which
+    patches are traced side by side, and so what the caches hold) is not the
+    one they were taken with."""
     try:
         with open(TRAFFIC) as f:
             rec = json.load(f)

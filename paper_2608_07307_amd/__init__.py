@@ -255,7 +255,7 @@ def results_to_numpy(t) -> np.ndarray:
 
 
 def profile(enable: bool):
-    """Start (True) or stop (False) timing trace-kernel launches; resets totals."""
+    """Start (True) or stop (False) timing the launches' ray kernels; resets totals."""
     L.check(_load().srp_profile(1 if enable else 0))
 
 

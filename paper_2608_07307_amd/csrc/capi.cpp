@@ -108,7 +108,7 @@ std::vector<float> diffuse_sets() {
     return t;
 }
 
-// Optional timing of the trace-kernel launches (HIP events on the launch stream),
+// Optional timing of the ray-kernel launches (HIP events on the launch stream),
 // and of each whole launch: from its staging upload through its result copy.
 struct Profile {
     bool on = false;
